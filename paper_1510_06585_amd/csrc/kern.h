@@ -221,10 +221,12 @@ struct NBodyArgs {
     float4* vel;            // [N] (w unused), updated in place
     float4* acc;            // [N] accelerations (unfused force kernel) or null
     int32_t N;
-    int32_t jsplit;         // wavefronts sharing one group of 64 bodies
+    int32_t jsplit;         // wavefronts sharing one group of bodies (nbody_group)
     float eps2, G, dt;
     int32_t pad;
 };
+// Bodies per work-group of the force kernel: 16, 32 or 64.
+int nbody_group(int64_t N);
 // Fused force + kick-drift (fused = true) or force only into acc.
 hipError_t launch_nbody_force(const NBodyArgs& a, bool fused, hipStream_t s, const char** kname);
 hipError_t launch_nbody_integrate(const NBodyArgs& a, hipStream_t s, const char** kname);

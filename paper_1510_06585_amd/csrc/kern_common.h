@@ -45,3 +45,11 @@ static __device__ __forceinline__ uint32_t wave_shl1(uint32_t v) {
 }
 
 static __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Orders a wavefront's LDS writes before its following LDS reads by other
+// lanes of the same wavefront.
+static __device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}

@@ -31,14 +31,6 @@ static_assert(kNP == 5825, "parameter count");
 // through a 16 x 64 LDS tile per wavefront.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Orders a wavefront's LDS writes before its following LDS reads by other
-// lanes of the same wavefront.
-static __device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 static __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }

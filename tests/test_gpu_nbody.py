@@ -94,3 +94,22 @@ def test_zero_iterations_leave_state():
     pos, vel = synth.nbody(9, 100)
     p, v = run_gpu(pos, vel, 0)
     assert (p == pos).all() and (v == vel).all()
+
+
+@pytest.mark.parametrize("N", [15, 17, 1023, 1025, 16383, 16384, 16385, 32767, 32768, 32801])
+@pytest.mark.parametrize("slices", [0, 3])
+def test_one_step_forces_around_group_and_slice_edges(N, slices):
+    """Groups of 16, 32 and 64 bodies, ragged last groups and stages, slices without a body.  A term
+    carries at most ~14 roundings (differences, d^2, v_rsq_f32 and its cube) and its sum passes at most
+    64 additions in a stage, N / (64 slices) + 1 across stages, 2 across lanes and 16 across slices:
+    |a - a_ref| <= (98 + N / (64 slices)) 2^-24 sum |term|, per component."""
+    pos, vel = synth.nbody(N, N)
+    _, v = run_gpu(pos, vel, 1, {"tile_h": slices} if slices else None, g=1.0, dt=1.0)
+    r = cuda(pos).double()
+    ref, mag = torch.empty(N, 3, dtype=torch.float64, device="cuda"), torch.empty(N, 3, dtype=torch.float64, device="cuda")
+    for i in range(0, N, 512):
+        d = r[None, :, :3] - r[i:i + 512, None, :3]
+        t = r[None, :, 3:] * d * ((d * d).sum(2, keepdim=True) + float(np.float32(EPS)) ** 2) ** -1.5
+        ref[i:i + 512], mag[i:i + 512] = t.sum(1), t.abs().sum(1)
+    err = np.abs(v[:, :3] - ref.cpu().numpy())
+    assert (err <= (98 + N / (64 * (slices or 16))) * 2.0 ** -24 * mag.cpu().numpy()).all()
