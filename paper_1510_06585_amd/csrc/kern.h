@@ -7,8 +7,12 @@
 namespace skel {
 
 constexpr int kMaxOps = 8;          // value stages per side of a fused image kernel
-constexpr int kBandOut = 252;       // output pixels per wavefront band (stencil kernels)
+constexpr int kBandOut = 248;       // output pixels per wavefront band (stencil kernels)
 constexpr int kBandPx = 256;        // pixels a wavefront loads per row (64 lanes x 4)
+inline int band_count(int64_t W, bool blur) {
+    const int bw = blur ? kBandOut : kBandPx;
+    return (int)((W + bw - 1) / bw);
+}
 
 // Value (non-moving) image stages inside a fused kernel.
 enum : uint8_t { IOP_NONE = 0, IOP_NOISE = 1, IOP_SOL = 2 };
@@ -21,6 +25,13 @@ struct OpList {
     uint8_t flip[kMaxOps];
     uint32_t seed[kMaxOps];
 };
+
+// Cache policy of a kernel's image streams.  A store marked as a stream does
+// not displace other data from the 256 MB memory-side cache, so the input,
+// or what the next launch reads, can stay there; marking the loads too pays
+// only where the input exceeds that cache anyway.
+enum : int32_t { STREAM_NONE = 0, STREAM_OUT = 1, STREAM_BOTH = 2 };
+constexpr int64_t kMallBytes = (int64_t)256 << 20;   // memory-side cache
 
 // One fused image kernel: pre-stages, an optional 5x5 blur, post-stages, an
 // optional histogram/sum epilogue.  The kernel iterates over coordinates u of
@@ -40,6 +51,7 @@ struct ImgGroupArgs {
     int32_t in_flip, out_flip;
     int32_t write_out;   // 0 for a reduce-only kernel
     int32_t hist_ks;     // log2 of the histogram copies per bin (see hist_copies_log2)
+    int32_t stream;          // STREAM_*
     const uint32_t* guard;   // while Loop: the launch does nothing when *guard == 0 (null: always runs)
     OpList pre, post;
 };
@@ -147,7 +159,7 @@ struct BatchArgs {
     int32_t has_hist;
     int32_t hist_ks;     // log2 copies per bin of the work-group histograms
     int32_t bins;        // values emitted are < bins
-    int32_t pad;
+    int32_t stream;      // STREAM_*
     uint32_t* part;      // histogram rows, one per tile group (ticket)
     uint32_t* counter;   // work-queue ticket counter (zeroed before launch)
     OpList pre, post;

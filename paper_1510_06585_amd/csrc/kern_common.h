@@ -16,20 +16,28 @@ static __device__ __forceinline__ __amdgpu_buffer_rsrc_t mk_rsrc(const void* p, 
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, SKEL_RSRC_WORD3);
 }
 
+// Cache policy of a stream's accesses (the nt bit of the instruction): a
+// non-temporal stream does not stay in the memory-side cache.
+enum { kTemporal = 0, kStream = 2 };
+
+template <int POLICY = kTemporal>
 static __device__ __forceinline__ u32x4 ld128(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, POLICY);
 }
 static __device__ __forceinline__ uint32_t ld32(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
+template <int POLICY = kTemporal>
 static __device__ __forceinline__ void st128(u32x4 v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, POLICY);
 }
+template <int POLICY = kTemporal>
 static __device__ __forceinline__ void st64(u32x2 v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, POLICY);
 }
+template <int POLICY = kTemporal>
 static __device__ __forceinline__ void st32(uint32_t v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, POLICY);
 }
 
 static __device__ __forceinline__ u16x2 as16(uint32_t v) { return __builtin_bit_cast(u16x2, v); }

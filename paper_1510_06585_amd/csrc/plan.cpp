@@ -346,7 +346,7 @@ skel_status resolve_config(const Linear& L, const Shape& sh, const skel_plan_opt
             c.auto_tile = true;
             bool blur = false;
             for (const Stage& s : L.st) blur |= s.op == SKEL_OP_BLUR5;
-            const int64_t nb = (sh.W + (blur ? kBandOut : kBandPx) - 1) / (blur ? kBandOut : kBandPx);
+            const int64_t nb = band_count(sh.W, blur);
             // Enough wavefront tiles to fill 256 CUs several times over.
             int th = 256;
             while (th > (blur ? 16 : 8) && nb * ((sh.H + th - 1) / th) < 4096) th /= 2;
@@ -474,24 +474,32 @@ int device_cu_count() {
 }
 
 // Default rows per tile.  With x = H * nbands / R, R the resident wavefronts
-// of the launch, x rows per tile fill the device exactly once.  Shorter tiles
-// leave a shorter tail: the wavefronts sharing a SIMD do not progress evenly
-// (the oldest issues first), so with a single round the last wavefront of each
-// SIMD runs alone at the end.  Taller tiles amortise the per-tile costs: the
-// two halo rows above and below a stencil tile, and the LDS histogram clear
-// and row store of a reduce work-group.  Measured on gfx950 over 512^2..8192^2
-// images, the best height grows like sqrt(x): 4 sqrt(x) for stencil tiles,
-// 3 sqrt(x) for reduce tiles, sqrt(x) otherwise (at least 2 rows).  When that
-// gives a round or more, the height is then raised just enough to make the
-// tile count a whole number of rounds: a few tiles over a round boundary form
-// a tail round of their own (8192^2 stencil tiles: 32 rows = 2.06 rounds ran
-// 5% slower than 34 rows = 1.94 rounds).
+// of the launch, x rows per tile fill the device exactly once.
+//  - Without a stencil and a histogram: 3 rows.  Such a wavefront issues all its
+//    loads at once and ends without waiting for its stores; in a longer tile the
+//    in-order counter of vector memory makes every load also wait for the stores
+//    before it (8192 x 8192 / 8700 x 8192 / 4289 x 2847, TB/s: 2 rows 6.2 / 5.8 / 5.2, 3 rows
+//    6.0 / 6.2 / 5.5, 4 rows 5.1 / 4.8 / 5.4, 16 rows 5.1 / 5.1 / 5.1).
+//  - Stencil tiles of large images (x >= 10): one round, x rounded up, for the
+//    fewest halo rows (8192^2 with a histogram: 69 rows 4400 GB/s, 50 rows 4240;
+//    4289 x 2847: 13 rows 2980, 8 rows 2570).
+//  - Otherwise 4 sqrt(x) rows for stencil tiles and 3 sqrt(x) for reduce tiles
+//    (at least 2): taller tiles amortise halo rows and the histogram's clear and
+//    row store, shorter ones leave a shorter tail (the oldest wavefronts of a SIMD
+//    issue first).  When that gives a round or more, the height is raised just
+//    enough to make the tile count a whole number of rounds: a few tiles over a
+//    round boundary form a tail round of their own.
 static int fitted_tile_h(const ImgGroupArgs& A, bool blur, bool hist, const Config& c) {
     if (A.W <= 0 || A.H <= 0) return 1;
+    if (!blur && !hist) return std::min(3, (int)A.H);
     const double resident = (double)img_waves_per_cu(A, blur, hist, c.wg, c.variant) * device_cu_count();
     const int64_t nb = std::max<int32_t>(1, A.nbands);
     const double x = (double)A.H * nb / std::max(1.0, resident);
-    const double k = blur ? 4.0 : (hist ? 3.0 : 1.0);
+    if (blur && x >= 10.0) {
+        const int64_t chunks = std::max<int64_t>(1, (int64_t)resident / nb);
+        return (int)std::min<int64_t>((A.H + chunks - 1) / chunks, A.H);
+    }
+    const double k = blur ? 4.0 : 3.0;
     int th = std::max(2, (int)std::lround(k * std::sqrt(x)));
     const double rounds = (double)nb * ((A.H + th - 1) / th) / std::max(1.0, resident);
     if (rounds >= 1.0) {
@@ -637,12 +645,16 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             }
             A.W = (int32_t)sh.W;
             A.H = (int32_t)sh.H;
-            const int bw = K.blur ? kBandOut : kBandPx;
-            A.nbands = (int32_t)((sh.W + bw - 1) / bw);
+            A.nbands = band_count(sh.W, K.blur);
             A.tile_h = c.auto_tile ? fitted_tile_h(A, K.blur, K.reduce, c) : c.tile_h;
             const int64_t chunks = (sh.H + A.tile_h - 1) / A.tile_h;
             A.ntiles = (sh.W == 0 || sh.H == 0) ? 0 : (int32_t)(A.nbands * chunks);
             A.write_out = 1;
+            // An intermediate or a while Loop's image is read by the next kernel,
+            // so only final images are streamed out.
+            A.stream = sh.W * sh.H * 4 >= kMallBytes ? STREAM_BOTH
+                       : K.dst == -2 && !L.is_while  ? STREAM_OUT
+                                                     : STREAM_NONE;
             A.hist_ks = hist_copies_log2(bins, kHistWgWords);
             A.bins = bins;
             K.bins = bins;
@@ -685,7 +697,7 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             memset(&A, 0, sizeof(A));
             A.W = (int32_t)sh.W;
             A.H = (int32_t)sh.H;
-            A.nbands = (int32_t)((sh.W + kBandPx - 1) / kBandPx);
+            A.nbands = band_count(sh.W, false);
             A.tile_h = c.auto_tile ? fitted_tile_h(A, false, true, c) : c.tile_h;
             const int64_t chunks = (sh.H + A.tile_h - 1) / A.tile_h;
             A.ntiles = (sh.W == 0 || sh.H == 0) ? 0 : (int32_t)(A.nbands * chunks);

@@ -455,8 +455,8 @@ def main():
         return
     st = kernel_stats(a.trace)
     tr = traffic(a.fetch, a.write)
-    src = os.path.join(HERE, "csrc", "kern_img.hip")
-    rec = {"kernel": FUSED_NAME, "source": "kern_img.hip",
+    src = os.path.join(HERE, "csrc", "kern_img_dev.h")
+    rec = {"kernel": FUSED_NAME, "source": "kern_img_dev.h",
            "source_sha256": hashlib.sha256(open(src, "rb").read()).hexdigest(),
            "bytes_per_launch": round(tr["bytes_per_launch"]),
            "algorithmic_bytes": 2 * 8192 * 8192 * 4 + 4128, **{k: round(v, 4) for k, v in tr.items()}}

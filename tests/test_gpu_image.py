@@ -65,6 +65,24 @@ def test_pipeline_mapreduce_odd_sizes(W, H):
         assert (h == rh).all() and (s == rs).all(), opt
 
 
+@pytest.mark.parametrize("W,H", [(w, 1 + i % 15) for i, w in enumerate(
+    (1, 2, 3, 4, 5, 7, 243, 244, 245, 247, 248, 249, 251, 252, 255, 256, 257, 493, 496, 497, 499, 508, 513, 746, 751))])
+@pytest.mark.parametrize("names", ["noise,solarise,blur5,mirror", "mirror,noise,blur5,noise", "noise,mirror",
+                                   "mirror,noise,solarise,mirror", "blur5"])
+def test_band_edges(W, H, names):
+    """Widths around the 248- and 256-pixel bands and their four-pixel lanes, rows around the groups of
+    the blur's six-slot ring; mirrored and plain noise, rows whose four-pixel groups are not aligned."""
+    img = synth.image(W * 31 + H, H, W)
+    stages = [(n, {"seed": 5 + i} if n == "noise" else {}) for i, n in enumerate(names.split(","))]
+    ref, rh, rs = oracle.run_image_pipeline(img, stages, "hist_sum")
+    for opt in ({}, {"tile_h": 7}, {"variant": 1}):
+        out, h, s = run_image(stages, img, "hist_sum", opt)
+        assert_image_equal(out, ref, f"{W}x{H} {names} {opt}")
+        assert (h == rh).all() and (s == rs).all(), opt
+        out, _, _ = run_image(stages, img, None, opt)
+        assert_image_equal(out, ref, f"{W}x{H} {names} {opt}, no reduce")
+
+
 @pytest.mark.parametrize("W,H", [(1, 1), (2, 2), (3, 7), (260, 3), (1000, 37)])
 def test_every_stage_alone_and_mirror_positions(W, H):
     img = synth.image(W + 100 * H, H, W)
