@@ -355,18 +355,22 @@ skel_status resolve_config(const Linear& L, const Shape& sh, const skel_plan_opt
         if (c.tile_h < 1 || c.tile_h > kMaxDim) return set_error(SKEL_EINVAL, "tile_h out of range");
         c.ept = 1;
     } else if (L.dom == DOM_F32) {
-        c.wg = o->wg ? o->wg : 256;
-        if (c.wg < 64 || c.wg > 1024 || c.wg % 64) return set_error(SKEL_EINVAL, "wg must be a multiple of 64 up to 1024");
+        // One vector per thread (10^7 elements: 6.7 TB/s, 4 vectors 6.3; with a sum
+        // 5.0 against 4.4), in 1024-lane groups from 2^20 vectors on.  Sums keep
+        // 256 lanes up to 2^23 vectors; beyond, 4 vectors in 1024 lanes, for
+        // fewer partials (5x10^7: 6.22 TB/s, one vector in 256 lanes 5.96).
         const int64_t nvec = (sh.n + 3) / 4;
-        c.ept = o->ept ? o->ept : (nvec >= ((int64_t)1 << 20) ? 4 : 1);
+        c.wg = o->wg ? o->wg : (nvec >= ((int64_t)1 << (L.red >= 0 ? 23 : 20)) ? 1024 : 256);
+        if (c.wg < 64 || c.wg > 1024 || c.wg % 64) return set_error(SKEL_EINVAL, "wg must be a multiple of 64 up to 1024");
+        c.ept = o->ept ? o->ept : (L.red >= 0 && nvec >= ((int64_t)1 << 23) ? 4 : 1);
         if (c.ept < 1 || c.ept > 64) return set_error(SKEL_EINVAL, "ept out of range");
         c.tile_h = 0;
     } else if (L.dom == DOM_GRAY) {
-        // one 16-byte vector per lane in 512-lane groups measured fastest on
-        // volumes of 1 to 60 MiB
-        c.wg = o->wg ? o->wg : 512;
+        // two 16-byte vectors per lane in 256-lane groups: 60 MiB 6.6 TB/s, one
+        // vector 6.2, four 6.5; volumes up to 8 MiB run alike at any of them
+        c.wg = o->wg ? o->wg : 256;
         if (c.wg < 64 || c.wg > 1024 || c.wg % 64) return set_error(SKEL_EINVAL, "wg must be a multiple of 64 up to 1024");
-        c.ept = o->ept ? o->ept : 1;
+        c.ept = o->ept ? o->ept : 2;
         if (c.ept < 1 || c.ept > 64) return set_error(SKEL_EINVAL, "ept out of range");
         c.tile_h = 0;
     } else if (L.dom == DOM_C32) {
@@ -561,6 +565,7 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
         for (int g = 0; g < nk; ++g) {
             ks[g].src = g == 0 ? -1 : ((g - 1) % 2);
             ks[g].dst = g == nk - 1 ? -2 : (g % 2);
+            ks[g].gray.stream = stream_policy(sh.n, g == nk - 1);
         }
         return SKEL_OK;
     }
@@ -652,9 +657,7 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             A.write_out = 1;
             // An intermediate or a while Loop's image is read by the next kernel,
             // so only final images are streamed out.
-            A.stream = sh.W * sh.H * 4 >= kMallBytes ? STREAM_BOTH
-                       : K.dst == -2 && !L.is_while  ? STREAM_OUT
-                                                     : STREAM_NONE;
+            A.stream = stream_policy(sh.W * sh.H * 4, K.dst == -2 && !L.is_while && !red_sep);
             A.hist_ks = hist_copies_log2(bins, kHistWgWords);
             A.bins = bins;
             K.bins = bins;
@@ -679,6 +682,7 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             A.n = sh.n;
             A.ept = c.ept;
             A.write_out = 1;
+            A.stream = stream_policy((1 + A.nops) * sh.n * 4, K.dst == -2 && !red_sep);
             const int64_t nvec = (sh.n + 3) / 4;
             K.grid = (int)((nvec + (int64_t)c.wg * c.ept - 1) / ((int64_t)c.wg * c.ept));
             K.name = "vec_chain";

@@ -69,7 +69,7 @@ std::vector<Config> enumerate_configs(const Linear& L, const Shape& sh) {
     }
     for (uint32_t m : masks) {
         if (L.dom == DOM_GRAY) {
-            for (int ept : {1, 8}) {
+            for (int ept : {1, 2, 8}) {
                 Config c = base;
                 c.fusion = k >= 1 ? SKEL_FUSE_MASK : SKEL_FUSE_ON;
                 c.split_mask = m;
