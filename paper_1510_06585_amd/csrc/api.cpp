@@ -172,7 +172,7 @@ skel_status run_image(skel_plan p, const skel_buffer* args, hipStream_t s) {
 // iteration's image (the input for i = 0) and writes out when max - 1 - i is
 // even, the plan's second image otherwise, so a loop that runs to its limit
 // ends in out; every kernel of an iteration is guarded by the device flag,
-// which the step kernel clears when the condition fails or the limit is
+// which the step at the end of the merge clears when the condition fails or the limit is
 // reached.  The host enqueues blocks of check_every iterations; after each
 // block it enqueues a 4-byte copy of the flag into a pinned slot and records
 // an event, then waits for the previous block's event and reads that block's
@@ -183,7 +183,7 @@ skel_status run_image(skel_plan p, const skel_buffer* args, hipStream_t s) {
 //
 // Carried reduce outputs (a carried_mask bit on hist or sum): the iteration's
 // kernels write that output into the plan's iteration buffer instead, and the
-// step kernel adds it to the caller's buffer, which is never cleared, so the
+// step adds it to the caller's buffer, which is never cleared, so the
 // result is the caller's initial content plus every iteration's partial
 // result (the merge by addition of Sec. 3.4).  The condition always reads the
 // iteration's own sums.  check_every < 0: the whole limit is enqueued with no
@@ -199,23 +199,24 @@ skel_status run_image_while(skel_plan p, const skel_buffer* args, hipStream_t s)
     const bool carry_sum = (L.loop_carried >> sum_arg) & 1u;
     uint32_t* it_hist = carry_hist ? p->witer_hist : hist;
     uint64_t* it_sum = carry_sum ? p->witer_sum : sum;
-    WhileMerge M;
-    memset(&M, 0, sizeof(M));
+    WhileStep step;
+    memset(&step, 0, sizeof(step));
+    step.state = p->wstate;
+    step.sum = it_sum;
+    step.count_out = count;
     if (carry_hist) {
-        M.it_hist = it_hist;
-        M.acc_hist = hist;
+        step.merge.it_hist = it_hist;
+        step.merge.acc_hist = hist;
     }
     if (carry_sum) {
-        M.it_sum = it_sum;
-        M.acc_sum = sum;
+        step.merge.it_sum = it_sum;
+        step.merge.acc_sum = sum;
     }
-    WhileCond wc;
-    memset(&wc, 0, sizeof(wc));
-    wc.channel = L.wcond.channel;
-    wc.cmp = L.wcond.cmp;
-    wc.threshold = L.wcond.threshold;
-    wc.max = L.while_max;
-    wc.kind = L.wcond.kind;
+    step.cond.channel = L.wcond.channel;
+    step.cond.cmp = L.wcond.cmp;
+    step.cond.threshold = L.wcond.threshold;
+    step.cond.max = L.while_max;
+    step.cond.kind = L.wcond.kind;
     const bool async = L.wcond.check_every < 0;
     const int every = async ? L.while_max : (L.wcond.check_every > 0 ? L.wcond.check_every : 8);
     HIP_TRY(launch_while_init(p->wstate, s));
@@ -249,10 +250,15 @@ skel_status run_image_while(skel_plan p, const skel_buffer* args, hipStream_t s)
                     F.nseg = 1;
                     F.nchunks = hist_chunks(k.grid, F.one.crows);
                     F.bins = k.bins;
-                    HIP_TRY(A.ntiles > 0 ? launch_hist_merge(F, s) : launch_hist_zero(F, s));
+                    F.step = step;
+                    if (A.ntiles > 0) {
+                        HIP_TRY(launch_hist_merge(F, s));
+                    } else {
+                        HIP_TRY(launch_hist_zero(F, s));
+                        HIP_TRY(launch_while_step(step, s));
+                    }
                 }
             }
-            HIP_TRY(launch_while_step(p->wstate, it_sum, wc, M, count, s));
         }
         if (it >= L.while_max || async) break;
         HIP_TRY(hipMemcpyAsync(p->h_flag + block % 2, p->wstate, sizeof(uint32_t), hipMemcpyDeviceToHost, s));

@@ -101,26 +101,11 @@ struct HistSeg {
     int32_t row_begin, nrows;
     int32_t crows, chunk_begin;
 };
-struct HistFinArgs {
-    const uint32_t* part;
-    const uint32_t* guard;   // as ImgGroupArgs::guard
-    const HistSeg* segs;   // device array of nseg segments, or null for `one`
-    HistSeg one;
-    int32_t nseg;
-    int32_t nchunks;       // chunks over all segments
-    int32_t bins;
-    int32_t pad;
-};
-// Rows per chunk for rows of 4 x bins words: 8 rows per thread of a
-// 1024-thread work-group.
-int hist_chunk_rows(int bins);
-inline int hist_chunks(int n, int crows) { return n > 0 ? (n + crows - 1) / crows : 0; }
-hipError_t launch_hist_merge(const HistFinArgs& a, hipStream_t s);
-hipError_t launch_hist_zero(const HistFinArgs& a, hipStream_t s);
 
 // While Loop on the device.  state[0] = 1 while the loop runs, state[1] =
 // iterations run, state[2..3] = the previous iteration's tested channel sum
-// (uint64).  init sets {1, 0}; step (after each iteration's merge) merges the
+// (uint64), state[4] = chunks of the running merge that are done.  init sets
+// {1, 0} and state[4] = 0; step (after each iteration's merge) merges the
 // iteration's carried reduce outputs into their accumulators, counts the
 // iteration, stores the count to *count_out and clears the flag when
 // count == max or the condition fails (kind 0: sum[channel] cmp threshold;
@@ -139,9 +124,34 @@ struct WhileMerge {
     const uint64_t* it_sum;
     uint64_t* acc_sum;      // [4]
 };
+struct WhileStep {
+    uint32_t* state;         // null: no step
+    const uint64_t* sum;     // the iteration's sums
+    WhileCond cond;
+    WhileMerge merge;
+    uint32_t* count_out;
+};
+struct HistFinArgs {
+    const uint32_t* part;
+    const uint32_t* guard;   // as ImgGroupArgs::guard
+    const HistSeg* segs;   // device array of nseg segments, or null for `one`
+    HistSeg one;
+    int32_t nseg;
+    int32_t nchunks;       // chunks over all segments
+    int32_t bins;
+    int32_t pad;
+    WhileStep step;        // taken by the launch's last chunk to finish
+};
+// Rows per chunk for rows of 4 x bins words: 8 rows per thread of a
+// 1024-thread work-group.
+int hist_chunk_rows(int bins);
+inline int hist_chunks(int n, int crows) { return n > 0 ? (n + crows - 1) / crows : 0; }
+hipError_t launch_hist_merge(const HistFinArgs& a, hipStream_t s);
+hipError_t launch_hist_zero(const HistFinArgs& a, hipStream_t s);
+
 hipError_t launch_while_init(uint32_t* state, hipStream_t s);
-hipError_t launch_while_step(uint32_t* state, const uint64_t* sum, const WhileCond& c, const WhileMerge& m,
-                             uint32_t* count_out, hipStream_t s);
+// The step on its own, for an iteration without a merge.
+hipError_t launch_while_step(const WhileStep& w, hipStream_t s);
 hipError_t launch_while_copy(const uint32_t* state, const void* src, void* dst, uint64_t bytes, uint32_t max,
                              hipStream_t s);
 

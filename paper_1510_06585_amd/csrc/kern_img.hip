@@ -52,6 +52,45 @@ static __device__ __forceinline__ u32x4 sum_rows(const uint32_t* base, int nrows
     return t;
 }
 
+// A value of the iteration's results.  SHARED: other work-groups of this launch
+// added to it with device-scope atomics.
+template <bool SHARED, typename T>
+static __device__ __forceinline__ T ld_result(const T* p) {
+    return SHARED ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+
+// One step of a while Loop by the whole work-group; the loop is running.
+template <bool SHARED>
+static __device__ __forceinline__ void while_step(const WhileStep& S) {
+    const WhileMerge& M = S.merge;
+    const WhileCond& c = S.cond;
+    uint32_t* const st = S.state;
+    if (M.acc_hist)
+        for (int b = threadIdx.x; b < 1024; b += blockDim.x) M.acc_hist[b] += ld_result<SHARED>(M.it_hist + b);
+    if (M.acc_sum && threadIdx.x < 4) M.acc_sum[threadIdx.x] += ld_result<SHARED>(M.it_sum + threadIdx.x);
+    if (threadIdx.x != 0) return;
+    const uint32_t n = st[1] + 1u;
+    st[1] = n;
+    *S.count_out = n;
+    uint64_t* prev = reinterpret_cast<uint64_t*>(st + 2);
+    const uint64_t s = ld_result<SHARED>(S.sum + c.channel);
+    bool go = true;
+    uint64_t v = s;
+    if (c.kind == 1) {
+        v = s >= *prev ? s - *prev : *prev - s;
+        *prev = s;
+    }
+    if (c.kind == 0 || n > 1u) {
+        switch (c.cmp) {
+            case 0: go = v > c.threshold; break;
+            case 1: go = v >= c.threshold; break;
+            case 2: go = v < c.threshold; break;
+            default: go = v <= c.threshold; break;
+        }
+    }
+    if (!go || n >= (uint32_t)c.max) st[0] = 0u;
+}
+
 // Merge (one launch after the kernels that wrote the rows): work-group k sums
 // the rows of chunk k.  A segment of one chunk gets its outputs written with
 // plain stores; the chunks of a longer segment add their non-zero counts, and
@@ -61,6 +100,7 @@ static __device__ __forceinline__ u32x4 sum_rows(const uint32_t* base, int nrows
 __global__ void __launch_bounds__(kFinThreads) hist_merge_kernel(const HistFinArgs F) {
     __shared__ u32x4 red[kFinThreads];
     __shared__ unsigned long long csum[4];
+    __shared__ bool last_chunk;
     if (F.guard && *F.guard == 0) return;
     const int k = blockIdx.x;
     const HistSeg& S = F.segs ? F.segs[seg_of(F, k)] : F.one;
@@ -101,6 +141,24 @@ __global__ void __launch_bounds__(kFinThreads) hist_merge_kernel(const HistFinAr
         else if (csum[threadIdx.x])
             atomicAdd((unsigned long long*)&S.sum[threadIdx.x], csum[threadIdx.x]);
     }
+    if (F.step.state == nullptr) return;
+    // A while Loop's step needs every chunk's result: the last chunk to finish
+    // takes it.  What it reads of other work-groups was added by device-scope
+    // atomics, which are performed before their wave's counter drops and which
+    // device-scope loads see, so the ticket needs no cache write-back (a
+    // __threadfence in every chunk made the iteration 3 us longer than a launch
+    // of its own).  Every work-group has read the guard before its ticket, so
+    // clearing the flag here stops later launches only.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) last_chunk = atomicAdd(&F.step.state[4], 1u) + 1u == gridDim.x;
+    __syncthreads();
+    if (!last_chunk) return;
+    if (threadIdx.x == 0) F.step.state[4] = 0u;
+    if (direct)
+        while_step<false>(F.step);
+    else
+        while_step<true>(F.step);
 }
 
 // Clears the histogram and sums of every segment (one work-group each).
@@ -116,43 +174,15 @@ __global__ void while_init_kernel(uint32_t* st) {
     if (threadIdx.x == 0) {
         st[0] = 1u;
         st[1] = 0u;
+        st[4] = 0u;
     }
 }
 
-// One work-group of kStepThreads threads.  Every thread reads the flag before
-// thread 0 may clear it, so a finished loop merges nothing and a running one
-// merges the whole histogram.
 constexpr int kStepThreads = 256;
-__global__ void __launch_bounds__(kStepThreads) while_step_kernel(uint32_t* st, const uint64_t* sum,
-                                                                 const WhileCond c, const WhileMerge M,
-                                                                 uint32_t* count_out) {
-    const uint32_t running = st[0];
-    __syncthreads();
-    if (running == 0u) return;
-    if (M.acc_hist)
-        for (int b = threadIdx.x; b < 1024; b += kStepThreads) M.acc_hist[b] += M.it_hist[b];
-    if (M.acc_sum && threadIdx.x < 4) M.acc_sum[threadIdx.x] += M.it_sum[threadIdx.x];
-    if (threadIdx.x != 0) return;
-    const uint32_t n = st[1] + 1u;
-    st[1] = n;
-    *count_out = n;
-    uint64_t* prev = reinterpret_cast<uint64_t*>(st + 2);
-    const uint64_t s = sum[c.channel];
-    bool go = true;
-    uint64_t v = s;
-    if (c.kind == 1) {
-        v = s >= *prev ? s - *prev : *prev - s;
-        *prev = s;
-    }
-    if (c.kind == 0 || n > 1u) {
-        switch (c.cmp) {
-            case 0: go = v > c.threshold; break;
-            case 1: go = v >= c.threshold; break;
-            case 2: go = v < c.threshold; break;
-            default: go = v <= c.threshold; break;
-        }
-    }
-    if (!go || n >= (uint32_t)c.max) st[0] = 0u;
+__global__ void __launch_bounds__(kStepThreads) while_step_kernel(const WhileStep S) {
+    const uint32_t running = S.state[0];
+    __syncthreads();   // every thread has read the flag before thread 0 may clear it
+    if (running != 0u) while_step<false>(S);
 }
 
 // Copies src to dst (nvec 16-byte vectors, then 4-byte words up to `words`)
@@ -265,6 +295,10 @@ int hist_chunk_rows(int bins) { return kSumUnroll * (kFinThreads / bins); }
 hipError_t launch_hist_merge(const HistFinArgs& a, hipStream_t s) {
     if (a.bins != 128 && a.bins != 256) return hipErrorInvalidValue;
     if (a.nchunks <= 0) return hipSuccess;
+    const WhileStep& w = a.step;
+    if (w.state && (w.cond.channel < 0 || w.cond.channel > 3 || w.cond.kind < 0 || w.cond.kind > 1 ||
+                    !w.merge.acc_hist != !w.merge.it_hist || !w.merge.acc_sum != !w.merge.it_sum))
+        return hipErrorInvalidValue;
     hipLaunchKernelGGL(hist_merge_kernel, dim3(a.nchunks), dim3(kFinThreads), 0, s, a);
     return hipGetLastError();
 }
@@ -289,11 +323,8 @@ hipError_t launch_while_init(uint32_t* state, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_while_step(uint32_t* state, const uint64_t* sum, const WhileCond& c, const WhileMerge& m,
-                             uint32_t* count_out, hipStream_t s) {
-    if (c.channel < 0 || c.channel > 3 || c.kind < 0 || c.kind > 1) return hipErrorInvalidValue;
-    if (!m.acc_hist != !m.it_hist || !m.acc_sum != !m.it_sum) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(while_step_kernel, dim3(1), dim3(kStepThreads), 0, s, state, sum, c, m, count_out);
+hipError_t launch_while_step(const WhileStep& w, hipStream_t s) {
+    hipLaunchKernelGGL(while_step_kernel, dim3(1), dim3(kStepThreads), 0, s, w);
     return hipGetLastError();
 }
 

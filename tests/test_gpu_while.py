@@ -304,3 +304,35 @@ def test_while_async_run_does_not_wait_and_reruns():
     assert (args[1].cpu().numpy() == ref2).all()
     assert (args[3].cpu().numpy().view(np.uint64) == rs2).all()
     p.destroy()
+
+
+@pytest.mark.parametrize("H", [1, 31, 32, 33, 63, 64, 65, 700])
+@pytest.mark.parametrize("body", ["blur", "nsbm"])
+def test_step_after_one_and_several_merge_chunks(body, H):
+    """One histogram row per image row (64-lane groups, one-row tiles), 32 or 64 rows per merge chunk:
+    the step runs in the only chunk or in the last of several to finish, with both reduce outputs
+    carried and the convergence condition; every run of the same plan counts afresh."""
+    img = synth.image(H, H, 200)
+    stages, thr, limit = BODIES[body], 3 * H, 7
+    x, prev, n = img, None, 0
+    rh, rs = np.full((4, 256), 7, np.uint32), np.full(4, 7, np.uint64)
+    while n < limit:
+        x, h, s = oracle.run_image_pipeline(x, stages, "hist_sum")
+        n, rh, rs = n + 1, rh + h, rs + s
+        if prev is not None and abs(int(s[1]) - prev) <= thr:
+            break
+        prev = int(s[1])
+    root = sk.LoopWhile(sk.image_chain(stages, "hist_sum"), limit, 1, ">", thr, 3, carried_mask=0b1100, kind="delta")
+    args = [cuda(img), torch.empty((H, 200, 4), dtype=torch.uint8, device="cuda"),
+            torch.full((4, 256), 7, dtype=torch.int32, device="cuda"),
+            torch.full((4,), 7, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")]
+    plan = sk.Plan(root, args, {"wg": 64, "tile_h": 1})
+    for _ in range(2):
+        args[2].fill_(7)
+        args[3].fill_(7)
+        plan.run(args)
+        torch.cuda.synchronize()
+        assert int(args[4].item()) == n
+        assert_image_equal(args[1].cpu().numpy(), x, f"count {n}")
+        assert (args[2].cpu().numpy().view(np.uint32) == rh).all()
+        assert (args[3].cpu().numpy().view(np.uint64) == rs).all()
