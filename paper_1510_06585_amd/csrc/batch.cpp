@@ -151,15 +151,6 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
     const Kernel& K = p->kernels[0];
     const int red = p->lin.red;
     const hipStream_t s = (hipStream_t)stream;
-    // Rows per tile: the plan's tile_h when it was given, else kBatchTileRows
-    // for every request.  With work-groups taking groups of adjacent tiles,
-    // short tiles keep the tail of the work list fine-grained for the cost
-    // of some halo recompute: on the 256-request benchmark batch, 31-34 rows
-    // measured best (1.735-1.744 ms), 23 or 48 rows 1.76 ms, 64 rows 1.79 ms,
-    // and the former per-request rule (ceil(H / 32) in [32, 128]) 1.78 ms.
-    constexpr int kBatchTileRows = 31;
-    auto tile_rows = [&](int64_t) -> int { return p->cfg.auto_tile ? kBatchTileRows : p->cfg.tile_h; };
-
     std::vector<int64_t> key;
     key.reserve((size_t)nreq * 6);
     for (int r = 0; r < nreq; ++r) {
@@ -185,6 +176,28 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
         const skel_buffer* b = args + (size_t)y * nargs;
         return a[0].shape[0] * a[0].shape[1] > b[0].shape[0] * b[0].shape[1];
     });
+    BatchArgs A;
+    memset(&A, 0, sizeof(A));
+    A.has_blur = K.blur;
+    A.in_flip = K.img.in_flip;
+    A.out_flip = K.img.out_flip;
+    A.has_hist = red >= 0;
+    A.hist_ks = hist_copies_log2(K.bins, kHistWgWords);
+    A.bins = K.bins;
+    // streamed loads as well measured slower (1634 against 1515 us on the 256-request batch)
+    A.stream = STREAM_OUT;
+    A.pre = K.img.pre;
+    A.post = K.img.post;
+    const int wg = K.wg;
+    const int max_grid = std::max(1, img_batch_blocks_per_cu(A, wg)) * device_cu_count();
+    // Rows per tile: the plan's tile_h when it was given, else kBatchTileRows
+    // for every request.  With work-groups taking groups of adjacent tiles,
+    // short tiles keep the tail of the work list fine-grained for the cost
+    // of some halo recompute: on the 256-request benchmark batch, 31-34 rows
+    // measured best, 23, 48 or 64 rows 1-3% slower; batches of 17 to 160 requests
+    // of 256 to 1178 pixels a side run alike from 16 to 31 rows.
+    constexpr int kBatchTileRows = 31;
+    const int tile_rows = p->cfg.auto_tile ? kBatchTileRows : p->cfg.tile_h;
     // Queued replays of the previous graph may still read the work list and
     // the histogram rows: wait for them before anything is rewritten.
     HIP_TRY(hipStreamSynchronize(s));
@@ -221,7 +234,7 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
         R.H = (int32_t)a[0].shape[0];
         R.W = (int32_t)a[0].shape[1];
         R.nbands = band_count(R.W, K.blur);
-        R.tile_h = tile_rows(R.H);
+        R.tile_h = tile_rows;
         R.nchunks = (R.H + R.tile_h - 1) / R.tile_h;
         R.tile_begin = (int32_t)tiles;
         const int64_t nt = (R.W > 0 && R.H > 0) ? (int64_t)R.nbands * R.nchunks : 0;
@@ -265,32 +278,13 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
     HIP_TRY(hipMemcpy(p->d_reqs, p->h_reqs, sizeof(BatchReq) * nreq, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(p->d_segs, p->h_segs, sizeof(HistSeg) * nreq, hipMemcpyHostToDevice));
 
-    BatchArgs A;
-    memset(&A, 0, sizeof(A));
     A.reqs = p->d_reqs;
     A.tile_req = p->d_tile_req;
     A.nreq = nreq;
     A.ntiles = (int32_t)tiles;
-    A.has_blur = K.blur;
-    A.in_flip = K.img.in_flip;
-    A.out_flip = K.img.out_flip;
-    A.has_hist = red >= 0;
-    A.hist_ks = hist_copies_log2(K.bins, kHistWgWords);
-    A.bins = K.bins;
-    // streamed loads as well measured slower (1634 against 1515 us on the 256-request batch)
-    A.stream = STREAM_OUT;
     A.part = p->b_rows;
     A.counter = p->d_counter;
-    A.pre = K.img.pre;
-    A.post = K.img.post;
-    hipDeviceProp_t prop;
-    HIP_TRY(hipGetDeviceProperties(&prop, p->device));
-    const int wg = K.wg;
-    int per_cu = img_batch_blocks_per_cu(A, wg);
-    if (per_cu < 1) per_cu = 1;
-    int grid = per_cu * prop.multiProcessorCount;
-    const int need = (int)(tiles / gw);
-    grid = std::max(1, std::min(grid, need));
+    const int grid = std::max(1, std::min(max_grid, (int)(tiles / gw)));
     p->batch_grid = grid;
 
     if (p->bexec) {
@@ -307,8 +301,8 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
     F.nseg = nreq;
     F.nchunks = (int32_t)chunks;
     F.bins = K.bins;
-    hipError_t e1 = launch_fill_u32(p->d_counter, 1, 0, p->cap_stream);
-    if (e1 == hipSuccess && red >= 0) e1 = launch_hist_zero(F, p->cap_stream);
+    hipError_t e1 = red >= 0 ? launch_hist_zero(F, p->cap_stream, p->d_counter)
+                             : launch_fill_u32(p->d_counter, 1, 0, p->cap_stream);
     hipError_t e2 = tiles > 0 ? launch_img_batch(A, grid, wg, p->cap_stream, &kname) : hipSuccess;
     hipError_t e3 = red >= 0 ? launch_hist_merge(F, p->cap_stream) : hipSuccess;
     hipGraph_t g = nullptr;

@@ -147,7 +147,8 @@ struct HistFinArgs {
 int hist_chunk_rows(int bins);
 inline int hist_chunks(int n, int crows) { return n > 0 ? (n + crows - 1) / crows : 0; }
 hipError_t launch_hist_merge(const HistFinArgs& a, hipStream_t s);
-hipError_t launch_hist_zero(const HistFinArgs& a, hipStream_t s);
+// Clears every segment's outputs, and *word when given.
+hipError_t launch_hist_zero(const HistFinArgs& a, hipStream_t s, uint32_t* word = nullptr);
 
 hipError_t launch_while_init(uint32_t* state, hipStream_t s);
 // The step on its own, for an iteration without a merge.

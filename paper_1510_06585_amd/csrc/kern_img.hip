@@ -161,9 +161,10 @@ __global__ void __launch_bounds__(kFinThreads) hist_merge_kernel(const HistFinAr
         while_step<true>(F.step);
 }
 
-// Clears the histogram and sums of every segment (one work-group each).
-__global__ void hist_zero_kernel(const HistFinArgs F) {
+// Clears the histogram and sums of every segment (one work-group each), and *word.
+__global__ void hist_zero_kernel(const HistFinArgs F, uint32_t* word) {
     if (F.guard && *F.guard == 0) return;
+    if (word && blockIdx.x == 0 && threadIdx.x == 0) *word = 0;
     const HistSeg& S = F.segs ? F.segs[blockIdx.x] : F.one;
     for (int b = threadIdx.x; b < 1024; b += blockDim.x)
         if (S.hist) S.hist[b] = 0;
@@ -220,18 +221,42 @@ int encode_ops(const OpList& l) {
     return e;
 }
 
+ImgEntries img_lite_0();
+ImgEntries img_lite_1();
+ImgEntries img_lite_2();
+ImgEntries img_lite_3();
+ImgEntries img_lite_4();
+ImgEntries img_lite_5();
+ImgEntries img_lite_6();
+ImgEntries img_lite_7();
+
+ImgEntries img_entries_lite(int k) {
+    ImgEntries (*const f[kLiteTables])() = {img_lite_0, img_lite_1, img_lite_2, img_lite_3,
+                                            img_lite_4, img_lite_5, img_lite_6, img_lite_7};
+    return f[k]();
+}
+
+// The kernels of a chain: one specialised for it (exact mirror flags first, then
+// run-time ones), else the interpreter.  The lite kernels take single images of
+// 4 columns or more only (W = 0: a batch).
 static const ImgEntry* find_entry(const OpList& pre, const OpList& post, bool blur, bool hist, int in_flip,
-                                  int out_flip, int variant) {
+                                  int out_flip, int variant, int W) {
     const int pe = encode_ops(pre), qe = encode_ops(post);
     const int fl = (in_flip ? 1 : 0) | (out_flip ? 2 : 0);
     if (variant == 0 && pre.n <= 6 && post.n <= 6) {
-        const ImgEntries t = !blur ? img_entries_point() : (hist ? img_entries_blur_hist() : img_entries_blur());
-        for (int pass = 0; pass < 2; ++pass)
+        const auto find = [&](const ImgEntries& t, int f) -> const ImgEntry* {
             for (int i = 0; i < t.n; ++i) {
                 const ImgEntry& e = t.e[i];
-                if (e.pre == pe && e.post == qe && e.blur == blur && e.hist == hist && e.fl == (pass ? -1 : fl))
-                    return &e;
+                if (e.pre == pe && e.post == qe && e.blur == blur && e.hist == hist && e.fl == f) return &e;
             }
+            return nullptr;
+        };
+        const ImgEntries t = !blur ? img_entries_point() : (hist ? img_entries_blur_hist() : img_entries_blur());
+        if (const ImgEntry* e = find(t, fl)) return e;
+        if (const ImgEntry* e = find(t, -1)) return e;
+        if (W >= 4)
+            for (int k = 0; k < kLiteTables; ++k)
+                if (const ImgEntry* e = find(img_entries_lite(k), -1)) return e;
     }
     const ImgEntries g = img_entries_generic();
     for (int i = 0; i < g.n; ++i)
@@ -240,7 +265,7 @@ static const ImgEntry* find_entry(const OpList& pre, const OpList& post, bool bl
 }
 
 int img_waves_per_cu(const ImgGroupArgs& a, bool blur, bool hist, int wg, int variant) {
-    const ImgEntry* e = find_entry(a.pre, a.post, blur, hist, a.in_flip, a.out_flip, variant);
+    const ImgEntry* e = find_entry(a.pre, a.post, blur, hist, a.in_flip, a.out_flip, variant, a.W);
     int nb = 0;
     if (!e || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(e->fn), wg, 0) !=
                   hipSuccess ||
@@ -252,13 +277,13 @@ int img_waves_per_cu(const ImgGroupArgs& a, bool blur, bool hist, int wg, int va
 }
 
 const char* img_kernel_name(const ImgGroupArgs& a, bool blur, bool hist, int variant) {
-    const ImgEntry* e = find_entry(a.pre, a.post, blur, hist, a.in_flip, a.out_flip, variant);
+    const ImgEntry* e = find_entry(a.pre, a.post, blur, hist, a.in_flip, a.out_flip, variant, a.W);
     return e ? e->name : "";
 }
 
 hipError_t launch_img_group(const ImgGroupArgs& a, bool blur, bool hist, int wg, int variant, hipStream_t s,
                             const char** kname, hipEvent_t t0, hipEvent_t t1) {
-    const ImgEntry* e = find_entry(a.pre, a.post, blur, hist, a.in_flip, a.out_flip, variant);
+    const ImgEntry* e = find_entry(a.pre, a.post, blur, hist, a.in_flip, a.out_flip, variant, a.W);
     if (!e) return hipErrorInvalidValue;
     if (kname) *kname = e->name;
     if (a.ntiles <= 0) {
@@ -282,7 +307,7 @@ hipError_t launch_img_group(const ImgGroupArgs& a, bool blur, bool hist, int wg,
 }
 
 hipError_t launch_img_batch(const BatchArgs& a, int grid, int wg, hipStream_t s, const char** kname) {
-    const ImgEntry* e = find_entry(a.pre, a.post, a.has_blur != 0, a.has_hist != 0, a.in_flip, a.out_flip, 0);
+    const ImgEntry* e = find_entry(a.pre, a.post, a.has_blur != 0, a.has_hist != 0, a.in_flip, a.out_flip, 0, 0);
     if (!e) return hipErrorInvalidValue;
     if (kname) *kname = e->name;
     if (wg != 256 && wg != 128 && wg != 64) return hipErrorInvalidValue;
@@ -303,14 +328,14 @@ hipError_t launch_hist_merge(const HistFinArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_hist_zero(const HistFinArgs& a, hipStream_t s) {
+hipError_t launch_hist_zero(const HistFinArgs& a, hipStream_t s, uint32_t* word) {
     if (a.nseg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(hist_zero_kernel, dim3(a.nseg), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(hist_zero_kernel, dim3(a.nseg), dim3(256), 0, s, a, word);
     return hipGetLastError();
 }
 
 int img_batch_blocks_per_cu(const BatchArgs& a, int wg) {
-    const ImgEntry* e = find_entry(a.pre, a.post, a.has_blur != 0, a.has_hist != 0, a.in_flip, a.out_flip, 0);
+    const ImgEntry* e = find_entry(a.pre, a.post, a.has_blur != 0, a.has_hist != 0, a.in_flip, a.out_flip, 0, 0);
     if (!e) return 0;
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(e->bfn), wg, 0) != hipSuccess)

@@ -104,12 +104,22 @@ struct Cols {
 // multiple of 4, so x ^ s = (g ^ (s & ~3)) + (j ^ (s & 3)) for the row's value s
 // and the first product needs one multiplication per lane: the four terms
 // (j ^ (s & 3)) c are the row's scalars.
-template <bool ALIGNED>
+// MODE: the group is known to be aligned, to be looked at pixel by pixel, or
+// (ANY_GROUP, an interior lane) aligned unless mirrored in rows of an odd width.
+enum { BY_PIXEL = 0, ALIGNED = 1, ANY_GROUP = 2 };
+template <int MODE>
 static __device__ __forceinline__ void hash4(uint32_t (&h)[4], uint32_t seed, bool fl, const Cols& C, int y, int W) {
+    if constexpr (MODE == ANY_GROUP) {
+        if (!fl || (W & 3) == 0)
+            hash4<ALIGNED>(h, seed, fl, C, y, W);
+        else
+            hash4<BY_PIXEL>(h, seed, fl, C, y, W);
+        return;
+    }
     const uint32_t S = seed ^ ((uint32_t)y << 16);
     const uint32_t s = S ^ (S >> 16);
     constexpr uint32_t c = 0x85EBCA6Bu;
-    if constexpr (ALIGNED) {
+    if constexpr (MODE == ALIGNED) {
         const uint32_t g = (uint32_t)(fl ? W - 4 - C.ub : C.ub);
         uint32_t t = (g ^ (s & ~3u)) * c;
         asm("" : "+v"(t));   // keeps the additions below from being folded back into four products
@@ -136,17 +146,17 @@ struct Px4 {
     uint32_t e[4], o[4];
 };
 
-template <bool ALIGNED>
+template <int MODE>
 static __device__ __forceinline__ void noise4(Px4& p, uint32_t seed, bool fl, const Cols& C, int y, int W) {
     uint32_t h[4];
-    hash4<ALIGNED>(h, seed, fl, C, y, W);
+    hash4<MODE>(h, seed, fl, C, y, W);
 #pragma unroll
     for (int i = 0; i < 4; ++i) noise_px(p.e[i], p.o[i], h[i]);
 }
-template <bool ALIGNED>
+template <int MODE>
 static __device__ __forceinline__ void noise_sol4(Px4& p, uint32_t seed, bool fl, const Cols& C, int y, int W) {
     uint32_t h[4];
-    hash4<ALIGNED>(h, seed, fl, C, y, W);
+    hash4<MODE>(h, seed, fl, C, y, W);
 #pragma unroll
     for (int i = 0; i < 4; ++i) noise_sol_px(p.e[i], p.o[i], h[i]);
 }
@@ -159,24 +169,24 @@ static __device__ __forceinline__ void sol4(Px4& p) {
 }
 
 // Value stages with a compile-time op sequence (ENC = sum op_k 4^k).
-template <int ENC, int K, bool ALIGNED>
+template <int ENC, int K, int MODE>
 static __device__ __forceinline__ void apply_const(const OpList& L, Px4& p, const Cols& C, int y, int W) {
     if constexpr (ENC != 0) {
         constexpr int op = ENC & 3;
         if constexpr (op == IOP_NOISE && ((ENC >> 2) & 3) == IOP_SOL) {
-            noise_sol4<ALIGNED>(p, L.seed[K], L.flip[K] != 0, C, y, W);
-            apply_const<(ENC >> 4), K + 2, ALIGNED>(L, p, C, y, W);
+            noise_sol4<MODE>(p, L.seed[K], L.flip[K] != 0, C, y, W);
+            apply_const<(ENC >> 4), K + 2, MODE>(L, p, C, y, W);
             return;
         } else if constexpr (op == IOP_NOISE) {
-            noise4<ALIGNED>(p, L.seed[K], L.flip[K] != 0, C, y, W);
+            noise4<MODE>(p, L.seed[K], L.flip[K] != 0, C, y, W);
         } else if constexpr (op == IOP_SOL) {
             sol4(p);
         }
-        apply_const<(ENC >> 2), K + 1, ALIGNED>(L, p, C, y, W);
+        apply_const<(ENC >> 2), K + 1, MODE>(L, p, C, y, W);
     }
 }
 
-template <int ENC, bool ALIGNED>
+template <int ENC, int MODE>
 static __device__ __forceinline__ void apply_ops(const OpList& L, Px4& p, const Cols& C, int y, int W) {
     if constexpr (ENC == kGeneric) {
         // Stage interpreter: the op list is a kernel argument, so every branch
@@ -184,16 +194,16 @@ static __device__ __forceinline__ void apply_ops(const OpList& L, Px4& p, const 
         for (int k = 0; k < L.n; ++k) {
             const int op = L.op[k];
             if (op == IOP_NOISE && k + 1 < L.n && L.op[k + 1] == IOP_SOL) {
-                noise_sol4<ALIGNED>(p, L.seed[k], L.flip[k] != 0, C, y, W);
+                noise_sol4<MODE>(p, L.seed[k], L.flip[k] != 0, C, y, W);
                 ++k;
             } else if (op == IOP_NOISE) {
-                noise4<ALIGNED>(p, L.seed[k], L.flip[k] != 0, C, y, W);
+                noise4<MODE>(p, L.seed[k], L.flip[k] != 0, C, y, W);
             } else if (op == IOP_SOL) {
                 sol4(p);
             }
         }
     } else {
-        apply_const<ENC, 0, ALIGNED>(L, p, C, y, W);
+        apply_const<ENC, 0, MODE>(L, p, C, y, W);
     }
 }
 
@@ -234,6 +244,7 @@ enum { HIST_NONE = 0, HIST_WG = 1, HIST_WG128 = 2 };
 constexpr int kEdgeLanes = 8;
 // Kinds of tiles (see band_tile's sweep).
 enum { INTERIOR = 0, EDGE_VEC = 1, EDGE_PX = 2 };
+constexpr int kByArgs = -1;   // a sweep's cache policy as the arguments give it
 constexpr int kHistWgChan = 2048;
 
 // Per-tile geometry and addressing of one image.
@@ -264,7 +275,10 @@ static __device__ __forceinline__ void add_hsum5(const uint32_t (&d)[4], uint32_
     B[3] = s3 + d[1] + B[3];
 }
 
-template <int PRE, int POST, bool BLUR, int HM>
+// LITE: the smaller variant of the kernels for the less common chains, with the
+// cache policy and the mirror flags read at run time and no path for images of
+// fewer than 4 columns.
+template <int PRE, int POST, bool BLUR, int HM, bool LITE>
 static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList& pre, const OpList& post,
                                                  int band, int y0, int y1, int lane, uint32_t* lh, int hks) {
     constexpr bool HIST = HM != HIST_NONE;
@@ -319,7 +333,7 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
     auto sweep = [&](auto kind_tag, auto aligned_tag, auto in_tag, auto out_tag) {
         constexpr int KIND = decltype(kind_tag)::value;
         constexpr bool I = KIND == INTERIOR;
-        constexpr bool AL = decltype(aligned_tag)::value;
+        constexpr int AL = decltype(aligned_tag)::value;
         constexpr int IN = decltype(in_tag)::value, OUT = decltype(out_tag)::value;   // cache policies
         Cols C;
         C.ub = ub;
@@ -354,7 +368,8 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
         auto load_row = [&](int yy) -> u32x4 {
             const uint32_t rowoff = (uint32_t)yy * (uint32_t)W * 4u;
             if constexpr (KIND != EDGE_PX) {
-                return ld128<IN>(rin, rowoff + in_vec);
+                if (IN == kByArgs) return V.stream == STREAM_BOTH ? ld128<kStream>(rin, rowoff + in_vec) : ld128(rin, rowoff + in_vec);
+                return ld128<IN == kByArgs ? kTemporal : IN>(rin, rowoff + in_vec);
             } else {
                 u32x4 r;
                 r.x = ld32(rin, rowoff + in_px[0]);
@@ -401,10 +416,10 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
                     } else {
                         v.x = fin[0]; v.y = fin[1]; v.z = fin[2]; v.w = fin[3];
                     }
-                    if (OUT != kTemporal && shared_line)
+                    if (OUT == kTemporal || shared_line || (OUT == kByArgs && V.stream == STREAM_NONE))
                         st128(v, rout, rowoff + out_vec);
                     else
-                        st128<OUT>(v, rout, rowoff + out_vec);
+                        st128<kStream>(v, rout, rowoff + out_vec);
                 } else if constexpr (!I) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -534,26 +549,37 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
     constexpr std::integral_constant<int, kTemporal> keep{};
     constexpr std::integral_constant<int, kStream> stream{};
     constexpr std::integral_constant<int, INTERIOR> inner{};
-    if (W < 4) {
-        sweep(std::integral_constant<int, EDGE_PX>{}, std::false_type{}, keep, keep);
+    constexpr std::integral_constant<int, BY_PIXEL> by_pixel{};
+    constexpr std::integral_constant<int, ALIGNED> aligned{};
+    if constexpr (LITE) {
+        constexpr std::integral_constant<int, kByArgs> by_args{};
+        if (interior)
+            sweep(inner, std::integral_constant<int, ANY_GROUP>{}, by_args, by_args);
+        else
+            sweep(std::integral_constant<int, EDGE_VEC>{}, by_pixel, keep, keep);
         return;
-    }
-    if (!interior) {
-        sweep(std::integral_constant<int, EDGE_VEC>{}, std::false_type{}, keep, keep);
-        return;
-    }
-    if constexpr ((PRE != 0 && PRE != 2) || (POST != 0 && POST != 2)) {   // a noise stage, or unknown
-        if ((W & 3) != 0 && (any_flip(pre) || any_flip(post))) {
-            sweep(inner, std::false_type{}, keep, stream);
+    } else {
+        if (W < 4) {
+            sweep(std::integral_constant<int, EDGE_PX>{}, by_pixel, keep, keep);
             return;
         }
+        if (!interior) {
+            sweep(std::integral_constant<int, EDGE_VEC>{}, by_pixel, keep, keep);
+            return;
+        }
+        if constexpr ((PRE != 0 && PRE != 2) || (POST != 0 && POST != 2)) {   // a noise stage, or unknown
+            if ((W & 3) != 0 && (any_flip(pre) || any_flip(post))) {
+                sweep(inner, by_pixel, keep, stream);
+                return;
+            }
+        }
+        if (V.stream == STREAM_BOTH)
+            sweep(inner, aligned, stream, stream);
+        else if (HIST || V.stream == STREAM_OUT)
+            sweep(inner, aligned, keep, stream);
+        else
+            sweep(inner, aligned, keep, keep);
     }
-    if (V.stream == STREAM_BOTH)
-        sweep(inner, std::true_type{}, stream, stream);
-    else if (HIST || V.stream == STREAM_OUT)
-        sweep(inner, std::true_type{}, keep, stream);
-    else
-        sweep(inner, std::true_type{}, keep, keep);
 }
 
 // Zeroes a work-group's histogram, 16 bytes per access.
@@ -596,7 +622,7 @@ static __device__ __forceinline__ void write_hist_row(uint32_t* lh, uint32_t* ro
 // output), which removes the per-row selects of the flipped data order;
 // FL = -1 reads them from the arguments.
 // Specialised stencil kernels are held to 128 VGPRs, four wavefronts per SIMD.
-template <int PRE, int POST, bool BLUR, bool HIST, int FL>
+template <int PRE, int POST, bool BLUR, bool HIST, int FL, bool LITE = false>
 __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_band_kernel(const ImgGroupArgs A) {
     __shared__ __attribute__((aligned(16))) uint32_t lh[HIST ? 4 * kHistWgChan : 1];
     if (A.guard && *A.guard == 0) return;   // a finished while Loop: the whole grid returns
@@ -623,10 +649,10 @@ __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_band
         const ImgView V{A.in, A.out, A.W, A.H, FL < 0 ? A.in_flip : (FL & 1), FL < 0 ? A.out_flip : (FL >> 1),
                         A.write_out, A.stream};
         if (HIST && A.bins == 128)
-            band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE>(V, A.pre, A.post, band, y0, y1, lane, lh,
+            band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, LITE>(V, A.pre, A.post, band, y0, y1, lane, lh,
                                                                        A.hist_ks);
         else
-            band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE>(V, A.pre, A.post, band, y0, y1, lane, lh,
+            band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, LITE>(V, A.pre, A.post, band, y0, y1, lane, lh,
                                                                     A.hist_ks);
     }
     if constexpr (HIST) {
@@ -690,10 +716,10 @@ __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_batc
             const ImgView V{R.in, R.out, R.W, R.H, FL < 0 ? A.in_flip : (FL & 1), FL < 0 ? A.out_flip : (FL >> 1),
                             1, A.stream};
             if (HIST && A.bins == 128)
-                band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE>(V, A.pre, A.post, band, y0, y1, lane, lh,
+                band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, false>(V, A.pre, A.post, band, y0, y1, lane, lh,
                                                                            A.hist_ks);
             else
-                band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE>(V, A.pre, A.post, band, y0, y1, lane, lh,
+                band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, false>(V, A.pre, A.post, band, y0, y1, lane, lh,
                                                                         A.hist_ks);
         }
         if constexpr (HIST) {
@@ -731,6 +757,13 @@ struct ImgEntry {
     SKEL_IMG_ENTRY(P, 0, true, Hh, 0, NAME), SKEL_IMG_ENTRY(P, 0, true, Hh, 2, NAME), \
         SKEL_IMG_ENTRY(P, 0, true, Hh, -1, NAME)
 
+// Chains of up to two value stages on either side of a stencil, or on their own
+// (5 = noise twice, 6 = solarise then noise): single images of 4 columns or more.
+#define SKEL_IMG_LITE(P, Q, B, Hh, NAME) {P, Q, B, Hh, -1, img_band_kernel<P, Q, B, Hh, -1, true>, nullptr, NAME}
+#define SKEL_IMG_LITE_PRE(P, Hh, NAME)                                                          \
+    SKEL_IMG_LITE(P, 1, true, Hh, NAME), SKEL_IMG_LITE(P, 2, true, Hh, NAME), SKEL_IMG_LITE(P, 5, true, Hh, NAME), \
+        SKEL_IMG_LITE(P, 6, true, Hh, NAME), SKEL_IMG_LITE(P, 9, true, Hh, NAME)
+
 struct ImgEntries {
     const ImgEntry* e;
     int n;
@@ -739,5 +772,7 @@ ImgEntries img_entries_point();       // no stencil
 ImgEntries img_entries_blur();        // stencil
 ImgEntries img_entries_blur_hist();   // stencil and histogram
 ImgEntries img_entries_generic();     // stage interpreter
+ImgEntries img_entries_lite(int k);   // the less common chains, kLiteTables of them
+constexpr int kLiteTables = 8;
 
 }  // namespace skel

@@ -615,6 +615,17 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
     skel_status st = segments(L, c, segs, red_sep);
     if (st) return st;
     const int nk = (int)segs.size();
+    // A solarise of values it cannot change (at most 127: after another solarise,
+    // mirrors and blurs in between) takes no part in a kernel.
+    std::vector<bool> idle(L.st.size(), false);
+    bool at_most_127 = false;
+    for (size_t i = 0; i < L.st.size(); ++i) {
+        if (L.st[i].op == SKEL_OP_NOISE) at_most_127 = false;
+        if (L.st[i].op == SKEL_OP_SOLARISE) {
+            idle[i] = at_most_127;
+            at_most_127 = true;
+        }
+    }
     for (int g = 0; g < nk; ++g) {
         Kernel K;
         K.first = segs[g].first;
@@ -639,14 +650,14 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
                 A.in_flip = mirrors(K.first, b);
                 A.out_flip = mirrors(b + 1, K.last);
                 for (int i = K.first; i < b; ++i)
-                    if (L.st[i].op == SKEL_OP_NOISE || L.st[i].op == SKEL_OP_SOLARISE) push_op(A.pre, L.st[i], mirrors(i + 1, b));
+                    if ((L.st[i].op == SKEL_OP_NOISE || L.st[i].op == SKEL_OP_SOLARISE) && !idle[i]) push_op(A.pre, L.st[i], mirrors(i + 1, b));
                 for (int i = b + 1; i < K.last; ++i)
-                    if (L.st[i].op == SKEL_OP_NOISE || L.st[i].op == SKEL_OP_SOLARISE) push_op(A.post, L.st[i], mirrors(b + 1, i));
+                    if ((L.st[i].op == SKEL_OP_NOISE || L.st[i].op == SKEL_OP_SOLARISE) && !idle[i]) push_op(A.post, L.st[i], mirrors(b + 1, i));
             } else {
                 A.in_flip = 0;
                 A.out_flip = mirrors(K.first, K.last);
                 for (int i = K.first; i < K.last; ++i)
-                    if (L.st[i].op == SKEL_OP_NOISE || L.st[i].op == SKEL_OP_SOLARISE) push_op(A.pre, L.st[i], mirrors(K.first, i));
+                    if ((L.st[i].op == SKEL_OP_NOISE || L.st[i].op == SKEL_OP_SOLARISE) && !idle[i]) push_op(A.pre, L.st[i], mirrors(K.first, i));
             }
             A.W = (int32_t)sh.W;
             A.H = (int32_t)sh.H;

@@ -65,6 +65,33 @@ def test_pipeline_mapreduce_odd_sizes(W, H):
         assert (h == rh).all() and (s == rs).all(), opt
 
 
+@pytest.mark.parametrize("pre", ["", "noise", "solarise", "noise,noise", "solarise,noise", "noise,solarise",
+                                 "solarise,solarise", "noise,solarise,noise"])
+@pytest.mark.parametrize("mirrors", [(), (0,), (1,), (0, 2), (1, 2)])
+def test_value_stages_on_both_sides_of_a_stencil(pre, mirrors):
+    """Every kernel of up to two value stages before and after the blur (and one list that only the
+    interpreter takes), mirrors before the stages, before the blur and at the end; solarise stages
+    that cannot change their input; values below 128 and up to 255 into the histogram."""
+    posts = ["", "noise", "solarise", "noise,noise", "solarise,noise", "noise,solarise", "mirror,noise"]
+    W, H = 517 + len(mirrors), 61
+    img = synth.image(len(pre) * 8 + sum(mirrors), H, W)
+    for k, post in enumerate(posts):
+        for stencil in (["blur5"], []) if k < 2 else (["blur5"],):
+            parts = [pre, ",".join(stencil), post]
+            for m in sorted(mirrors, reverse=True):
+                parts.insert(m, "mirror")
+            names = [n for q in parts for n in q.split(",") if n]
+            if not names:
+                continue
+            stages = [(n, {"seed": 11 * i + k} if n == "noise" else {}) for i, n in enumerate(names)]
+            ref, rh, rs = oracle.run_image_pipeline(img, stages, "hist_sum")
+            out, h, s = run_image(stages, img, "hist_sum")
+            assert_image_equal(out, ref, f"{names}")
+            assert (h == rh).all() and (s == rs).all(), names
+            out, _, _ = run_image(stages, img)
+            assert_image_equal(out, ref, f"{names}, no reduce")
+
+
 @pytest.mark.parametrize("W,H", [(w, 1 + i % 15) for i, w in enumerate(
     (1, 2, 3, 4, 5, 7, 243, 244, 245, 247, 248, 249, 251, 252, 255, 256, 257, 493, 496, 497, 499, 508, 513, 746, 751))])
 @pytest.mark.parametrize("names", ["noise,solarise,blur5,mirror", "mirror,noise,blur5,noise", "noise,mirror",
