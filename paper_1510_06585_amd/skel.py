@@ -231,10 +231,25 @@ def _buf_array(bufs):
     return arr, len(bufs)
 
 
+_raw_stream = None   # torch's current-stream handle of a device, without a Stream object
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device.  Building a torch
+    Stream object for it takes 2.5 us, 40% of a small run's host time; the raw
+    getter 0.1."""
+    global _raw_stream
+    import torch
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", False)
+    if _raw_stream and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream_handle(stream):
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return ctypes.c_void_p(_current_stream())
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)

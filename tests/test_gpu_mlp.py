@@ -73,6 +73,61 @@ def test_gradient_matches_oracle(n):
           f"{max(maxerr(gg[lo:hi], gr[lo:hi]) for lo, hi in blocks):.2e}")
 
 
+@pytest.mark.parametrize("n", [15, 16, 17, 4095, 4097, 9001, 20480, 20481])
+def test_group_and_dispatch_edges(n):
+    """Ragged last groups of 16, work-groups with one and with several groups (gradient from 4097
+    samples on, forward from 20481).  A term of a sum
+    over the samples passes at most 4 matrix steps per group, n / 4096 + 1 groups and 66 row
+    additions, 2^-24 of the terms' magnitudes each: far inside the bounds of the smaller batches."""
+    X, t, theta = batch(500 + n, n)
+    y = torch.empty(n, dtype=torch.float32, device="cuda")
+    sk.mlp_forward(dev(theta), dev(X), y)
+    g = torch.empty(5825, dtype=torch.float32, device="cuda")
+    L = torch.empty(1, dtype=torch.float32, device="cuda")
+    sk.mlp_grad(dev(theta), dev(X), dev(t), g, L)
+    torch.cuda.synchronize()
+    th = theta.astype(np.float64)
+    ref, _ = mlp.forward(th, X.astype(np.float64))
+    assert maxerr(y.cpu().numpy(), ref) <= 2e-5
+    Lr, gr = mlp.loss_and_grad(th, X.astype(np.float64), t.astype(np.float64))
+    assert abs(float(L.cpu()[0]) - Lr) <= 1e-5 * abs(Lr)
+    gg = g.cpu().numpy()
+    for lo, hi in ((0, 1536), (1536, 1600), (1600, 5696), (5696, 5760), (5760, 5824), (5824, 5825)):
+        assert relerr(gg[lo:hi], gr[lo:hi]) <= 1e-4 and maxerr(gg[lo:hi], gr[lo:hi]) <= 2e-4, (lo, hi)
+
+
+def test_gradients_on_several_streams_and_threads():
+    """Gradients of different batches and sizes in flight on four streams from four host threads: each
+    has the workspace to itself until its own work is done."""
+    import threading
+    jobs = [batch(700 + k, n) for k, n in enumerate((256, 4097, 31, 1024))]
+    want, got = [], [[] for _ in jobs]
+    for X, t, theta in jobs:
+        g, L = torch.empty(5825, device="cuda"), torch.empty(1, device="cuda")
+        sk.mlp_grad(dev(theta), dev(X), dev(t), g, L)
+        want.append(g)
+    torch.cuda.synchronize()
+
+    def work(k):
+        X, t, theta = (dev(a) for a in jobs[k])
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.default_stream())
+        for _ in range(12):
+            g, L = torch.empty(5825, device="cuda"), torch.empty(1, device="cuda")
+            sk.mlp_grad(theta, X, t, g, L, stream=s)
+            got[k].append(g)
+        s.synchronize()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    for k, w in enumerate(want):
+        assert len(got[k]) == 12 and all(torch.equal(g, w) for g in got[k]), k
+
+
 def test_adam_step_elementwise():
     """One Adam step from the same fp32 gradient, at steps 1, 2 and 50: every
     first and second moment within 1e-6 of the block's largest value, and
