@@ -190,17 +190,23 @@ template <int ENC, int MODE>
 static __device__ __forceinline__ void apply_ops(const OpList& L, Px4& p, const Cols& C, int y, int W) {
     if constexpr (ENC == kGeneric) {
         // Stage interpreter: the op list is a kernel argument, so every branch
-        // below is uniform across the wavefront.
-        for (int k = 0; k < L.n; ++k) {
-            const int op = L.op[k];
-            if (op == IOP_NOISE && k + 1 < L.n && L.op[k + 1] == IOP_SOL) {
-                noise_sol4<MODE>(p, L.seed[k], L.flip[k] != 0, C, y, W);
-                ++k;
-            } else if (op == IOP_NOISE) {
-                noise4<MODE>(p, L.seed[k], L.flip[k] != 0, C, y, W);
-            } else if (op == IOP_SOL) {
-                sol4(p);
-            }
+        // below is uniform across the wavefront.  Codes, flips and seeds are
+        // selected from scalar registers: loads from the argument at index k would
+        // put a memory latency into every stage of every row.
+        uint32_t codes = 0, flips = 0, seed[kMaxOps];
+#pragma unroll
+        for (int k = 0; k < kMaxOps; ++k) {
+            codes |= (uint32_t)(k < L.n ? L.op[k] : 0) << (2 * k);
+            flips |= (uint32_t)(L.flip[k] != 0) << k;
+            seed[k] = L.seed[k];
+        }
+        for (int k = 0; codes != 0; ++k, codes >>= 2, flips >>= 1) {
+            uint32_t sd = seed[0];
+#pragma unroll
+            for (int j = 1; j < kMaxOps; ++j) sd = k == j ? seed[j] : sd;
+            const uint32_t op = codes & 3u;
+            if (op == IOP_NOISE) noise4<MODE>(p, sd, (flips & 1u) != 0, C, y, W);
+            if (op == IOP_SOL) sol4(p);
         }
     } else {
         apply_const<ENC, 0, MODE>(L, p, C, y, W);
@@ -276,8 +282,8 @@ static __device__ __forceinline__ void add_hsum5(const uint32_t (&d)[4], uint32_
 }
 
 // LITE: the smaller variant of the kernels for the less common chains, with the
-// cache policy and the mirror flags read at run time and no path for images of
-// fewer than 4 columns.
+// cache policy and the mirror flags read at run time; only the interpreter takes
+// images of fewer than 4 columns.
 template <int PRE, int POST, bool BLUR, int HM, bool LITE>
 static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList& pre, const OpList& post,
                                                  int band, int y0, int y1, int lane, uint32_t* lh, int hks) {
@@ -553,7 +559,9 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
     constexpr std::integral_constant<int, ALIGNED> aligned{};
     if constexpr (LITE) {
         constexpr std::integral_constant<int, kByArgs> by_args{};
-        if (interior)
+        if (PRE == kGeneric && W < 4)
+            sweep(std::integral_constant<int, EDGE_PX>{}, by_pixel, keep, keep);
+        else if (interior)
             sweep(inner, std::integral_constant<int, ANY_GROUP>{}, by_args, by_args);
         else
             sweep(std::integral_constant<int, EDGE_VEC>{}, by_pixel, keep, keep);
@@ -716,10 +724,10 @@ __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_batc
             const ImgView V{R.in, R.out, R.W, R.H, FL < 0 ? A.in_flip : (FL & 1), FL < 0 ? A.out_flip : (FL >> 1),
                             1, A.stream};
             if (HIST && A.bins == 128)
-                band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, false>(V, A.pre, A.post, band, y0, y1, lane, lh,
+                band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, PRE == kGeneric>(V, A.pre, A.post, band, y0, y1, lane, lh,
                                                                            A.hist_ks);
             else
-                band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, false>(V, A.pre, A.post, band, y0, y1, lane, lh,
+                band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, PRE == kGeneric>(V, A.pre, A.post, band, y0, y1, lane, lh,
                                                                         A.hist_ks);
         }
         if constexpr (HIST) {
@@ -749,7 +757,7 @@ struct ImgEntry {
 };
 
 #define SKEL_IMG_ENTRY(P, Q, B, Hh, FL, NAME) \
-    {P, Q, B, Hh, FL, img_band_kernel<P, Q, B, Hh, FL>, img_batch_kernel<P, Q, B, Hh, FL>, NAME}
+    {P, Q, B, Hh, FL, img_band_kernel<P, Q, B, Hh, FL, P == kGeneric>, img_batch_kernel<P, Q, B, Hh, FL>, NAME}
 // Without a stencil the input is never mirrored (mirrors fold into the
 // output address), so those chains need FL 0 and 2 only.
 #define SKEL_IMG_POINT(P, Hh, NAME) SKEL_IMG_ENTRY(P, 0, false, Hh, 0, NAME), SKEL_IMG_ENTRY(P, 0, false, Hh, 2, NAME)

@@ -356,11 +356,11 @@ skel_status resolve_config(const Linear& L, const Shape& sh, const skel_plan_opt
         c.ept = 1;
     } else if (L.dom == DOM_F32) {
         // One vector per thread (10^7 elements: 6.7 TB/s, 4 vectors 6.3; with a sum
-        // 5.0 against 4.4), in 1024-lane groups from 2^20 vectors on.  Sums keep
-        // 256 lanes up to 2^23 vectors; beyond, 4 vectors in 1024 lanes, for
-        // fewer partials (5x10^7: 6.22 TB/s, one vector in 256 lanes 5.96).
+        // 32.9 us against 36.9), in 1024-lane groups from 2^20 vectors on (8x10^6
+        // with a sum: 25.4 us, 256 lanes 26.5).  Sums of 2^23 vectors or more take
+        // 4 per thread, for fewer partials (32x10^6: 84.5 us, one vector 87.6).
         const int64_t nvec = (sh.n + 3) / 4;
-        c.wg = o->wg ? o->wg : (nvec >= ((int64_t)1 << (L.red >= 0 ? 23 : 20)) ? 1024 : 256);
+        c.wg = o->wg ? o->wg : (nvec >= ((int64_t)1 << 20) ? 1024 : 256);
         if (c.wg < 64 || c.wg > 1024 || c.wg % 64) return set_error(SKEL_EINVAL, "wg must be a multiple of 64 up to 1024");
         c.ept = o->ept ? o->ept : (L.red >= 0 && nvec >= ((int64_t)1 << 23) ? 4 : 1);
         if (c.ept < 1 || c.ept > 64) return set_error(SKEL_EINVAL, "ept out of range");
@@ -487,24 +487,26 @@ int device_cu_count() {
 //  - Stencil tiles of large images (x >= 10): one round, x rounded up, for the
 //    fewest halo rows (8192^2 with a histogram: 69 rows 4400 GB/s, 50 rows 4240;
 //    4289 x 2847: 13 rows 2980, 8 rows 2570).
-//  - Otherwise 4 sqrt(x) rows for stencil tiles and 3 sqrt(x) for reduce tiles
-//    (at least 2): taller tiles amortise halo rows and the histogram's clear and
-//    row store, shorter ones leave a shorter tail (the oldest wavefronts of a SIMD
-//    issue first).  When that gives a round or more, the height is raised just
-//    enough to make the tile count a whole number of rounds: a few tiles over a
-//    round boundary form a tail round of their own.
+//  - Stencil tiles of smaller images: half a round, two work-groups on every CU;
+//    a few tiles more, and some CUs run a third (fused chain, us: 2048^2 10 rows
+//    12.1, 8 rows 13.4; 1000 x 4000 10 rows 11.9, 9 rows 14.5; 1799 x 1125 5 rows
+//    8.7, 6 rows 9.0).
+//  - Otherwise 3 sqrt(x) rows for reduce tiles (at least 2): taller tiles amortise
+//    the histogram's clear and row store, shorter ones leave a shorter tail (the
+//    oldest wavefronts of a SIMD issue first).  When that gives a round or more,
+//    the height is raised just enough to make the tile count a whole number of
+//    rounds: a few tiles over a round boundary form a tail round of their own.
 static int fitted_tile_h(const ImgGroupArgs& A, bool blur, bool hist, const Config& c) {
     if (A.W <= 0 || A.H <= 0) return 1;
     if (!blur && !hist) return std::min(3, (int)A.H);
     const double resident = (double)img_waves_per_cu(A, blur, hist, c.wg, c.variant) * device_cu_count();
     const int64_t nb = std::max<int32_t>(1, A.nbands);
     const double x = (double)A.H * nb / std::max(1.0, resident);
-    if (blur && x >= 10.0) {
-        const int64_t chunks = std::max<int64_t>(1, (int64_t)resident / nb);
-        return (int)std::min<int64_t>((A.H + chunks - 1) / chunks, A.H);
+    if (blur) {
+        const int64_t chunks = std::max<int64_t>(1, (int64_t)(x >= 10.0 ? resident : resident / 2) / nb);
+        return (int)std::min<int64_t>(std::max<int64_t>(2, (A.H + chunks - 1) / chunks), A.H);
     }
-    const double k = blur ? 4.0 : 3.0;
-    int th = std::max(2, (int)std::lround(k * std::sqrt(x)));
+    int th = std::max(2, (int)std::lround(3.0 * std::sqrt(x)));
     const double rounds = (double)nb * ((A.H + th - 1) / th) / std::max(1.0, resident);
     if (rounds >= 1.0) {
         const int64_t chunks = std::max<int64_t>(1, (int64_t)(std::lround(rounds) * resident) / nb);
