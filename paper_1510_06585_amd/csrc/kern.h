@@ -236,12 +236,14 @@ struct FftArgs {
     int32_t nfft;        // transforms in the batch
     int32_t dir1, dir2;  // -1 forward, +1 inverse
     float scale1;        // applied to a stage's pass-B result (1/65536 after an inverse)
+    int32_t stream;      // STREAM_* of a natural-order result
 };
 constexpr int kFftPoints = 65536;
 // Row stride, in complex elements, of the transposed layout T[k2][n1] that
 // passes exchange through plan scratch: 256 + 16 keeps every row on a 128-byte
 // line boundary while breaking the power-of-two stride of the column runs.
 constexpr int kFftTRow = 256 + 16;
+int fft_cols(int64_t nfft);   // columns (rows) of a transform per work-group
 hipError_t launch_fft_pass(const FftArgs& a, int mode, hipStream_t s);
 const char* fft_pass_name(int mode);
 

@@ -584,8 +584,8 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             Kernel K;
             K.first = first;
             K.last = last;
-            K.wg = 512;
-            K.grid = (int)(sh.n * 8);
+            K.wg = 16 * fft_cols(sh.n);
+            K.grid = (int)(sh.n * (256 / fft_cols(sh.n)));
             K.fft_mode = mode;
             memset(&K.fft, 0, sizeof(K.fft));
             K.fft.dir1 = dir(i);
@@ -609,6 +609,7 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
         for (int g = 0; g < nk; ++g) {
             ks[g].src = g == 0 ? -1 : ((g - 1) % 2);
             ks[g].dst = g == nk - 1 ? -2 : (g % 2);
+            ks[g].fft.stream = g == nk - 1 ? STREAM_OUT : STREAM_NONE;
         }
         return SKEL_OK;
     }

@@ -68,6 +68,17 @@ def test_fft_round_trip_and_closed_forms():
     assert (np.linalg.norm(back - z, axis=-1) / np.linalg.norm(z, axis=-1)).max() < 2e-5
 
 
+@pytest.mark.parametrize("B", [1, 7, 8, 31, 32, 33, 257])
+def test_work_group_widths_and_parts(B):
+    """8, 16 and 32 columns per work-group (below 8, below 32, from 32 transforms on) and a batch that
+    runs in two parts, one transform longer than the other; fused and unfused."""
+    x = synth.complex_batch(synth.SEED_FFT + B, B)
+    for opt in (None, {"fusion": sk.FUSE_OFF}) if B < 200 else (None,):
+        _check(x, ["fft", "ifft"], opt)
+        if B < 200:
+            _check(x, ["ifft"], opt)
+
+
 def test_fft_batch_of_64_and_rejections():
     x = synth.complex_batch(synth.SEED_FFT, 64)
     _check(x, ["fft", "ifft"])
