@@ -22,12 +22,12 @@
 // it, W_N^(n1 m) as one root per thread times one of a 16 x 32 LDS table.
 //
 // What bounds it: the three phases of a work-group (load, transform, store) against
-// HBM.  A third of the VALU operations went (element i of a thread lies a constant
-// distance from element 0, which loads and stores carry in a scalar offset; the
-// twiddles are table reads) with no change in time at 512 transforms, while streamed
-// results and runs of at most 256 transforms, whose intermediates then partly stay
-// in the memory-side cache, took FFT -> IFFT of 512 transforms from 318 to 297 us
-// and of 64 from 47.7 to 41.0.
+// HBM.  Constant element distances carried in scalar offsets and twiddles read from
+// tables took the VALU instructions of the three modes from 1457 / 2040 / 884 to
+// 1028 / 1709 / 747 with no change in time at 512 transforms.  With streamed results
+// and runs of at most 256 transforms, whose intermediates then partly stay in the
+// memory-side cache, FFT -> IFFT of 512 transforms went from 309 to 299 us, of 256
+// from 160 to 152, of 64 from 47.7 to 41.2; without the runs it is 318 us at 512.
 #include "kern_common.h"
 #include "kern.h"
 

@@ -41,9 +41,10 @@ import json
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-FUSED = "img_band_kernel<9, 0, true, true, 2>"
+# Kernel-name keys stop before the end of the argument list where more arguments follow.
+FUSED = "img_band_kernel<9, 0, true, true, 2"
 FUSED_NAME = "img_noise_sol_blur_reduce"
-COPY = "img_band_kernel<0, 0, false, false, 0>"
+COPY = "img_band_kernel<0, 0, false, false, 0"
 COPY_BYTES = 2 * 8192 * 8192 * 4
 COMMANDS = (
     "rocprofv3 --kernel-trace --stats -d DIR -o fused8192 --output-format csv -- python3 bench.py --no-extras "
@@ -111,7 +112,10 @@ COMMAND_WHILE = ("rocprofv3 --kernel-trace --stats -d DIR -o while8192 --output-
 COMMAND_MLP = ("rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_VALU_MFMA_BUSY_CYCLES SQ_INSTS_VALU SQ_BUSY_CYCLES "
                "-d DIR -o mfma --output-format csv -- python3 bench.py --mlp-profile-run")
 HBM_PEAK_GBS = 8000.0
-NBODY_PEAK_GPAIRS = 256 * 64 * 2.4 / 13.0   # 13 VALU issues per pair
+# 64 pairs per wavefront take 39 SIMD cycles: 3 sub (2.25 cycles each measured), 6 fma (2.5),
+# 3 mul (2.37) and one v_rsq_f32 (10); the fp32 operations of two wavefronts share issue slots.
+NBODY_PAIR_CYCLES = 39.0
+NBODY_PEAK_GPAIRS = 256 * 4 * 64 * 2.4 / NBODY_PAIR_CYCLES
 
 
 def row_work():
@@ -122,18 +126,18 @@ def row_work():
     import synth
     sides = synth.batch_sides(synth.SEED_BATCH, 256)
     batch_bytes = sum(2 * s * s * 4 + 4128 for s in sides)
-    fft_bytes = 2 * 512 * 65536 * 8
+    fft_bytes = 2 * 256 * 65536 * 8
     return [
         # the bench times the batch autotuner's choice last (30 runs), after
         # the tuner's own 30 candidates and the default plan
-        ("img_batch_kernel<9, 0, true, true, 2>", "256 uneven requests, noise>solarise>blur>mirror + histogram "
+        ("img_batch_kernel<9, 0, true, true, 2", "256 uneven requests, noise>solarise>blur>mirror + histogram "
          "(the autotuned plan's 30 timed runs)", "hbm", batch_bytes, 30),
-        ("fft_pass_kernel<0>", "pass A, 512 x 65536 complex fp32", "hbm", fft_bytes, 0),
-        ("fft_pass_kernel<1>", "fused pass B+A, 512 x 65536 complex fp32", "hbm", fft_bytes, 0),
-        ("fft_pass_kernel<2>", "pass B, 512 x 65536 complex fp32", "hbm", fft_bytes, 0),
+        ("fft_pass_kernel<0", "pass A, 256 x 65536 complex fp32 (half of a 512-transform run)", "hbm", fft_bytes, 0),
+        ("fft_pass_kernel<1", "fused pass B+A, 256 x 65536 complex fp32", "hbm", fft_bytes, 0),
+        ("fft_pass_kernel<2", "pass B, 256 x 65536 complex fp32", "hbm", fft_bytes, 0),
         ("gray_chain_kernel", "Segmentation, 240 x 512 x 512 u8", "hbm", 2 * 240 * 512 * 512, 0),
-        ("nbody_force_kernel<true>", "N-body force + kick-drift, 65536 bodies", "alu", 65536 * 65536, 0),
-        ("nbody_force_kernel<false>", "N-body force only, 65536 bodies", "alu", 65536 * 65536, 0),
+        ("nbody_force_kernel<true", "N-body force + kick-drift, 65536 bodies", "alu", 65536 * 65536, 0),
+        ("nbody_force_kernel<false", "N-body force only, 65536 bodies", "alu", 65536 * 65536, 0),
     ]
 
 
@@ -150,8 +154,8 @@ def last_dispatches(dispatch_csv, key, last):
 def row_roofline(stats, dispatch_csv=None):
     out = ["", "## Rooflines of the kernels that serve one workload each", "",
            "Achieved = work per launch / rocprof average duration (of the timed runs' dispatches where the "
-           "kernel also serves other runs); peaks: HBM 8 TB/s, N-body 256 CUs x 64 lanes x 2.4 GHz / 13 VALU "
-           "issues per pair.", "",
+           "kernel also serves other runs); peaks: HBM 8 TB/s, N-body 1024 SIMDs x 64 lanes x 2.4 GHz / 39 "
+           "issue cycles per pair.", "",
            "| kernel | workload | work per launch | avg us | achieved | peak | frac |", "|---|---|---|---|---|---|---|"]
     for key, what, kind, work, last in row_work():
         r = next((x for x in stats if key in x["name"]), None)
@@ -206,7 +210,7 @@ def while_phases(path):
 
 COMMAND_DRIVER = ("rocprofv3 --kernel-trace --stats -d DIR -o driver --output-format csv -- python3 bench.py "
                   "--gpus 1 --steps 20 --warmup 5")
-PLAIN_FIRST = "img_band_kernel<1, 0, false, false, 0>"   # noise alone: the plain plan's first kernel
+PLAIN_FIRST = "img_band_kernel<1, 0, false, false, 0"   # noise alone: the plain plan's first kernel
 
 
 def driver_phase(dispatch_csv, steps):
@@ -278,18 +282,18 @@ def other_work():
     launch, unit name) of the kernels `bench.py --counters-run` launches."""
     import synth
     sides = synth.batch_sides(synth.SEED_BATCH, 256)
-    n_fft = 512 * 65536
+    n_fft = 256 * 65536
     N = 65536
     return [
-        ("img_batch_kernel<9, 0, true, true, 2>", "256 uneven requests, noise>solarise>blur>mirror + histogram",
+        ("img_batch_kernel<9, 0, true, true, 2", "256 uneven requests, noise>solarise>blur>mirror + histogram",
          sum(2 * s * s * 4 + 4128 for s in sides), sum(s * s for s in sides), "pixel"),
-        ("fft_pass_kernel<0>", "FFT pass A, 512 x 65536 complex fp32", 2 * n_fft * 8, n_fft, "element"),
-        ("fft_pass_kernel<1>", "FFT fused pass B+A", 2 * n_fft * 8, n_fft, "element"),
-        ("fft_pass_kernel<2>", "FFT pass B", 2 * n_fft * 8, n_fft, "element"),
+        ("fft_pass_kernel<0", "FFT pass A, 256 x 65536 complex fp32", 2 * n_fft * 8, n_fft, "element"),
+        ("fft_pass_kernel<1", "FFT fused pass B+A", 2 * n_fft * 8, n_fft, "element"),
+        ("fft_pass_kernel<2", "FFT pass B", 2 * n_fft * 8, n_fft, "element"),
         ("vec_chain_kernel", "saxpy, 5 x 10^7 fp32 (read v, w; write out)", 12 * 50_000_000, 50_000_000,
          "element"),
         ("gray_chain_kernel", "Segmentation, 240 x 512 x 512 u8", 2 * 240 * 512 * 512, 240 * 512 * 512, "voxel"),
-        ("nbody_force_kernel<true>", "N-body force + kick-drift, 65536 bodies (one step)",
+        ("nbody_force_kernel<true", "N-body force + kick-drift, 65536 bodies (one step)",
          4 * N * 16, N * N, "pair"),
     ]
 
@@ -327,7 +331,8 @@ def other_summary(fetch_csv, write_csv, sq_csv):
         out += ["", "## VALU work (SQ counters, mean per dispatch)", "",
                 "VALU lane-instructions per unit = SQ_INSTS_VALU x 64 / units.  Issue share = "
                 f"(SQ_INSTS_VALU x 4 cycles / {SIMDS} SIMDs) / (SQ_BUSY_CYCLES / {SQ_ENGINES} engines): the "
-                "fraction of the busy cycles in which each SIMD issues a VALU instruction.", "",
+                "fraction of the busy cycles in which each SIMD issues a VALU instruction, above 1 where simple fp32 "
+                "operations of two wavefronts share an issue slot.", "",
                 "| kernel | units | SQ_WAVES | SQ_INSTS_VALU | VALU per unit | SQ_INSTS_SALU | SQ_INSTS_LDS | "
                 "SQ_LDS_BANK_CONFLICT | SQ_BUSY_CYCLES | issue share |", "|---|---|---|---|---|---|---|---|---|---|"]
         for key, what, algo, units, unit in other_work() + [(COPY, "copy", 0, 8192 * 8192, "pixel")]:
@@ -389,8 +394,8 @@ def main():
               "asynchronous while plan with the convergence condition and both reduce outputs carried (each "
               "after the warm-up floor, then 10 timed runs; both count as \"while plan\" below), the same body "
               "with the sums read back by the host after every iteration and the body alone, unchecked.  Per "
-              "iteration a while plan launches the image kernel, the histogram merge and the step kernel "
-              "(one work-group: the carried merges, the count and the condition); per run one init kernel "
+              "iteration a while plan launches the image kernel and the histogram merge, whose last chunk also does "
+              "the step (the carried merges, the count and the condition); per run one init kernel "
               "and one final guarded copy.", "",
               "| kernel | calls | avg us | min us | max us |", "|---|---|---|---|---|"]
         for r in stats:
