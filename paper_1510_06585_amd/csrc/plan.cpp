@@ -321,12 +321,6 @@ skel_status derive_shape(const Linear& L, const skel_buffer* proto, int32_t narg
     return set_error(SKEL_ETYPE, "cannot tell the domain of the chain");
 }
 
-static int pow2_floor(int64_t v) {
-    int p = 1;
-    while ((int64_t)p * 2 <= v) p *= 2;
-    return p;
-}
-
 skel_status resolve_config(const Linear& L, const Shape& sh, const skel_plan_opts* o, Config& c) {
     c = Config();
     skel_plan_opts d;
@@ -385,7 +379,6 @@ skel_status resolve_config(const Linear& L, const Shape& sh, const skel_plan_opt
         if (c.tile_h < 1 || c.tile_h > 16) return set_error(SKEL_EINVAL, "N-body j-slices must be 1..16");
         c.wg = 64 * c.tile_h;
         c.ept = 1;
-        (void)pow2_floor;
     }
     return SKEL_OK;
 }

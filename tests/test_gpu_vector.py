@@ -136,3 +136,21 @@ def test_saxpy_near_the_2gib_limit():
     2^31-byte vector limit, ragged against the 4-element vectors."""
     n = ((1 << 31) - 64) // 4 - 3
     check([("saxpy", {"a": 1.5})], n, 17, {}, reduce=None)
+
+
+@pytest.mark.parametrize("far", [4, 800], ids=["lanes", "wavefronts"])
+@pytest.mark.parametrize("n", [4096, 1 << 22, 1 << 25])
+def test_sum_keeps_ones_beside_a_cancelling_pair(n, far):
+    """A pair of +-2^26 in two lanes (or two wavefronts) of the first work-group and ones elsewhere:
+    fp32 adds across lanes would round lane sums of 4 off beside 2^26, fp64 adds keep them and every
+    partial is a whole number below 2^24, so the sum is exact.  256- and 1024-lane groups, 1 and 4 vectors
+    per lane."""
+    v = np.ones(n, np.float32)
+    for step in range(0, n, max(n // 4, 4096)):   # the two lanes' other vectors too
+        v[step:step + 4] = 0.0
+        v[step + far:step + far + 4] = 0.0
+    ones = int(v.sum(dtype=np.float64))
+    v[0], v[far] = 2.0 ** 26, -2.0 ** 26
+    assert float(np.float32(ones)) == ones
+    _, s = run_chain([("saxpy", {"a": 1.0})], v, [np.zeros(n, np.float32)], "sum")
+    assert s == ones
