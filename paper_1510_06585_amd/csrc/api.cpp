@@ -483,6 +483,11 @@ namespace {
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 }  // namespace
 
+static int tile_groups(const Kernel& k, int tile_h) {
+    const int tiles = k.img.nbands * ((k.img.H + tile_h - 1) / tile_h), waves = k.wg / 64;
+    return (tiles + waves - 1) / waves;
+}
+
 skel_status noalloc_prepare(skel_plan p, const skel_buffer* args, int32_t nargs, size_t cap, NoallocLayout& L) {
     skel_status st = check_args(p, args, nargs);
     if (st) return st;
@@ -522,6 +527,19 @@ skel_status noalloc_prepare(skel_plan p, const skel_buffer* args, int32_t nargs,
                 off += align256(sizeof(uint32_t) * 4 * (size_t)k.bins * (size_t)std::max(1, k.grid));
             }
     }
+    if (off > cap && L.has_hrows) {
+        const Kernel& k = p->kernels.back();   // the reduce comes last
+        const int64_t most = k.reduce && k.blur ? noalloc_max_groups(k, p->cfg) : k.grid;
+        const auto end = [&](int64_t groups) {
+            return L.off_hrows + align256(sizeof(uint32_t) * 4 * (size_t)k.bins * (size_t)std::max<int64_t>(1, groups));
+        };
+        if (most < k.grid && end(most) <= cap)
+            for (int t = k.img.tile_h + 1; t <= k.img.H && !L.tile_h; ++t)
+                if (tile_groups(k, t) <= most) {
+                    L.tile_h = t;
+                    off = end(tile_groups(k, t));
+                }
+    }
     L.total = off;
     if (off > cap)
         return set_error(SKEL_EUNSUPPORTED,
@@ -538,6 +556,14 @@ skel_status noalloc_run(skel_plan p, const skel_buffer* args, void* stream, char
     for (int k = 0; k < L.nimg; ++k) p->scratch[k] = region + L.off_img[k];
     if (L.has_partials) p->partials = (float*)(region + L.off_partials);
     if (L.has_hrows) p->hrows = (uint32_t*)(region + L.off_hrows);
+    Kernel* const last = L.tile_h ? &p->kernels.back() : nullptr;
+    const int saved_tile = last ? last->img.tile_h : 0, saved_tiles = last ? last->img.ntiles : 0;
+    const int saved_grid = last ? last->grid : 0;
+    if (last) {
+        last->grid = tile_groups(*last, L.tile_h);
+        last->img.ntiles = last->img.nbands * ((last->img.H + L.tile_h - 1) / L.tile_h);
+        last->img.tile_h = L.tile_h;
+    }
     const hipStream_t s = S(stream);
     skel_status st = SKEL_OK;
     switch (p->lin.dom) {
@@ -550,6 +576,11 @@ skel_status noalloc_run(skel_plan p, const skel_buffer* args, void* stream, char
     p->scratch[1] = saved_scr[1];
     p->partials = saved_partials;
     p->hrows = saved_hrows;
+    if (last) {
+        last->img.tile_h = saved_tile;
+        last->img.ntiles = saved_tiles;
+        last->grid = saved_grid;
+    }
     return st;
 }
 

@@ -111,6 +111,12 @@ skel_status resolve_config(const Linear& lin, const Shape& sh, const skel_plan_o
 // Builds the kernel list of (lin, sh, cfg); SKEL_EINVAL if the configuration
 // is not valid for this chain (e.g. two stencils forced into one kernel).
 skel_status build_kernels(const Linear& lin, const Shape& sh, const Config& cfg, std::vector<Kernel>& ks);
+// Work-groups, one histogram row each, up to which an allocation-free run makes
+// room for a stencil kernel with a histogram: those of bands of 252 pixels and
+// default tiles of 4 sqrt(x) rows, the sizes by which that entry point accepts a
+// plan.  Where the 248-pixel bands and the default tiles need more groups than
+// that and the rows no longer fit, the run takes taller tiles.
+int64_t noalloc_max_groups(const Kernel& K, const Config& cfg);
 // The partition-validity predicate (Sec. 3.1 constraints, adapted): true when
 // the configuration is admissible for this chain and shape.
 bool config_valid(const Linear& lin, const Shape& sh, const Config& cfg);
@@ -170,6 +176,7 @@ struct NoallocLayout {
     size_t off_img[2] = {0, 0};
     bool has_partials = false, has_hrows = false;
     size_t off_partials = 0, off_hrows = 0;
+    int tile_h = 0;   // taller tiles of the reduce kernel, or 0 for the plan's own
     size_t total = 0;
 };
 // Checks the arguments as skel_plan_run does, then lays out the plan's scratch;

@@ -141,3 +141,34 @@ def test_rejects_plans_beyond_its_scope_or_size():
     arr, n = sk.skel._buf_array([_fake([8, 9, 4], sk.U8, 1 << 40), _fake([8, 9, 4], sk.U8, 2 << 40)])
     assert lib.skel_plan_run_noalloc(plan.handle, arr, n, None) == sk.skel.ESHAPE
     plan.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,W,options,fits", [(7000, 250, {"tile_h": 1, "wg": 64}, True),
+                                              (8191, 252, {"tile_h": 1, "wg": 64}, True),
+                                              (8193, 252, {"tile_h": 1, "wg": 64}, False),
+                                              (8000, 249, {"tile_h": 3, "wg": 64}, True),
+                                              (5461, 756, {"tile_h": 2, "wg": 64}, False)])
+def test_histogram_rows_at_the_scratch_limit(H, W, options, fits):
+    """Widths where a band more than (W + 251) / 252 doubles or tops up the histogram rows (4 KB each):
+    what fits by (W + 251) / 252 bands runs, with the results of the ordinary run before and after; one
+    row more does not."""
+    img = synth.image(H, H, W)
+    a, b = _image_args(img, "hist_sum"), _image_args(img, "hist_sum")
+    plan = sk.Plan(sk.image_chain([("blur5", {})], "hist_sum"), a, options)
+    plan.run(a)
+    ref, d = _host(a), plan.describe()
+    if fits:
+        plan.run_noalloc(b)
+        for r, g in zip(ref, _host(b)):
+            assert (r == g).all()
+    else:
+        with pytest.raises(sk.SkelError) as e:
+            plan.run_noalloc(b)
+        assert e.value.status == sk.EUNSUPPORTED
+    assert plan.describe() == d
+    a[2].fill_(9)
+    plan.run(a)
+    for r, g in zip(ref, _host(a)):
+        assert (r == g).all()
+    plan.destroy()
