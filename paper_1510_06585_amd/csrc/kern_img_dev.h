@@ -13,8 +13,11 @@
 // rows above and below its rows.  Halo pixels are recomputed from the input,
 // never exchanged.
 //
-// What bounds it: the memory system, not the 43 VALU operations per pixel of the
-// noise, solarise, blur chain (cutting 1.5 of them changed no time).  Streamed
+// What bounds it: both sides at once.  The fused MapReduce moves 5.0 TB/s on 8192^2
+// and issues VALU operations (42.5 per pixel in the loop, 48 with halo rows and
+// epilogue) in 82% of its cycles; an uneven batch, with more halo rows and part
+// bands (53 per pixel), in 96%.  1.5 operations per pixel less changed neither
+// time measurably; the streams below did.  Streamed
 // stores (nt) keep the output out of the memory-side cache: the fused MapReduce
 // on 8192^2 133 -> 121 us with streamed loads besides, 4289 x 2847 pointwise
 // 4.3 -> 5.4 TB/s.  A streamed store of part of a 128-byte line costs more than it
