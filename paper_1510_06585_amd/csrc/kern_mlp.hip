@@ -17,7 +17,8 @@
 // parameters come in as 16-byte loads all in flight, and rows of 64 units are 68
 // words apart in LDS, which lets a lane read four consecutive inputs of a product
 // at once and keeps the 16 rows of a read on different banks (64 apart they
-// shared one).  Gradient of 256 samples 21.2 -> 9.3 us, of 16384 28.9 -> 21.7;
+// shared one).  Gradient kernel of 256 samples 5.9 us (8.0 with the parameters
+// taking a way through private memory, 21.2 with 16 samples per wavefront);
 // the rows' sum 4.0 -> 3.0 and 84.7 -> 8.2 (256 rows at most instead of 1024).
 // Parameter layout: W1 [64][24], b1 [64], W2 [64][64], b2 [64], W3 [64], b3.
 #include "kern_common.h"
@@ -34,10 +35,11 @@ static_assert(kNP == 5825, "parameter count");
 
 // Matrix-core formulation.  v_mfma_f32_16x16x4f32 computes D[16x16] +=
 // A[16x4] B[4x16] over a wavefront: lane l supplies A[l%16][l/16] and
-// B[l/16][l%16] and holds D[4(l/16)+r][l%16] in accumulator register r.  One
-// wavefront owns 16 samples; a 16 x K by K x 64 product is 4 output tiles of
-// K/4 steps.  Activations are turned from the D layout into the A layout
-// through a 16 x 64 LDS tile per wavefront.
+// B[l/16][l%16] and holds D[4(l/16)+r][l%16] in accumulator register r.  The
+// four wavefronts of a work-group share 16 samples and take 16 of a layer's 64
+// units each: a 16 x K by K x 16 product of K/4 steps per wavefront and layer.
+// Activations are turned from the D layout into the A layout through 16 x 64
+// LDS tiles, rows 68 words apart, which the work-group shares.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 static __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
@@ -53,33 +55,52 @@ struct MlpSmem {
     float b1[kH1], b2[kH2], W3[kH2], b3;
 };
 
-// Rows of ROW floats, each 16-byte piece one thread's; all loads are issued
-// before the first store.  The source needs 4-byte alignment only.
+// Rows of ROW floats, each 16-byte piece one thread's, in two steps: `fetch` only
+// issues the loads (a thread past the last piece reads that one again), `store`
+// writes LDS.  The pieces stay in registers in between; filled under a predicate
+// they went through private memory, one memory latency after another.  The
+// source needs 4-byte alignment only.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int ROWS, int ROW, int STRIDE>
-static __device__ __forceinline__ void load_rows(float* dst, const float* src) {
-    constexpr int pieces = ROWS * ROW / 4, per = (pieces + 64 * kWaves - 1) / (64 * kWaves);
-    float4 v[per];
+struct Rows {
+    static constexpr int pieces = ROWS * ROW / 4, per = (pieces + 64 * kWaves - 1) / (64 * kWaves);
+    f32x4 v[per];
+    __device__ __forceinline__ void fetch(const float* src) {
 #pragma unroll
-    for (int i = 0; i < per; ++i) {
-        const int p = threadIdx.x + i * 64 * kWaves;
-        if (p < pieces) __builtin_memcpy(&v[i], src + 4 * p, 16);
+        for (int i = 0; i < per; ++i) {
+            const int p = min((int)threadIdx.x + i * 64 * kWaves, pieces - 1);
+            v[i] = *reinterpret_cast<const f32x4u*>(src + 4 * p);
+        }
     }
+    __device__ __forceinline__ void store(float* dst) const {
 #pragma unroll
-    for (int i = 0; i < per; ++i) {
-        const int p = threadIdx.x + i * 64 * kWaves, row = 4 * p / ROW;
-        if (p < pieces) *reinterpret_cast<float4*>(dst + row * STRIDE + (4 * p - row * ROW)) = v[i];
+        for (int i = 0; i < per; ++i) {
+            const int p = threadIdx.x + i * 64 * kWaves, row = 4 * p / ROW;
+            if ((i + 1) * 64 * kWaves <= pieces || p < pieces)   // only a last round is partial
+                *reinterpret_cast<f32x4*>(dst + row * STRIDE + (4 * p - row * ROW)) = v[i];
+        }
     }
-}
+};
 
-static __device__ __forceinline__ void load_params(MlpSmem& S, const float* params) {
-    const int k = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const float u = params[(q == 0 ? oB1 : (q == 1 ? oB2 : oW3)) + k];
-    const float b3 = params[oB3];
-    load_rows<kH2, kH1, kR2>(S.W2, params + oW2);
-    load_rows<kH1, kIn, kR1>(S.W1, params + oW1);
-    if (q < 3) (q == 0 ? S.b1 : (q == 1 ? S.b2 : S.W3))[k] = u;
-    if (threadIdx.x == 0) S.b3 = b3;
-}
+struct Params {
+    Rows<kH2, kH1, kR2> w2;
+    Rows<kH1, kIn, kR1> w1;
+    float u, b3;
+    __device__ __forceinline__ void fetch(const float* params) {
+        const int k = threadIdx.x & 63, q = threadIdx.x >> 6;
+        w2.fetch(params + oW2);
+        w1.fetch(params + oW1);
+        u = params[(q == 0 ? oB1 : (q == 1 ? oB2 : oW3)) + k];
+        b3 = params[oB3];
+    }
+    __device__ __forceinline__ void store(MlpSmem& S) const {
+        const int k = threadIdx.x & 63, q = threadIdx.x >> 6;
+        w2.store(S.W2);
+        w1.store(S.W1);
+        if (q < 3) (q == 0 ? S.b1 : (q == 1 ? S.b2 : S.W3))[k] = u;
+        if (threadIdx.x == 0) S.b3 = b3;
+    }
+};
 
 // Products of a 16 x K operand whose rows this lane's c selects (A) with K x 16
 // (B), both read as four consecutive k per lane: step (q, j) uses k = 16 q + 4 g + j.
@@ -98,11 +119,15 @@ static __device__ __forceinline__ f32x4 dot64(const float* A, const float* B, in
     return acc[0] + acc[1];
 }
 
-// A row of X as the first layer's operand: features 6 g .. 6 g + 5 of sample
-// `row` (zeros when row < 0); step s uses k = 6 g + s.
-static __device__ __forceinline__ void load_x(const float* X, int row, int g, float (&xa)[6]) {
+// A row of X as the first layer's operand: features 6 g .. 6 g + 5 of sample `row`,
+// zeros unless `in` (the row is read all the same); step s uses k = 6 g + s.
+static __device__ __forceinline__ void load_x(const float* X, int row, bool in, int g, float (&xa)[6]) {
+    const float* const x = X + (size_t)row * kIn + 6 * g;
+    float v[6];
 #pragma unroll
-    for (int s = 0; s < 6; ++s) xa[s] = row >= 0 ? X[(size_t)row * kIn + 6 * g + s] : 0.0f;
+    for (int s = 0; s < 6; ++s) v[s] = x[s];
+#pragma unroll
+    for (int s = 0; s < 6; ++s) xa[s] = in ? v[s] : 0.0f;
 }
 
 // Tile t (units 16 t .. 16 t + 15) of the first layer's pre-activations, D
@@ -133,8 +158,8 @@ static __device__ __forceinline__ float sum16(float p) {
     return p;
 }
 
-// A work-group's wavefronts share 16 samples at a time, a tile each (256 samples
-// 10.0 -> 4.8 us; 16 samples per wavefront instead measured 20 us at 16384).
+// A work-group's wavefronts share 16 samples at a time, a tile each (back to back,
+// 256 samples 4.1 us and 16384 samples 5.0; 16 samples per wavefront 9.8 and 10.0).
 __global__ void __launch_bounds__(64 * kWaves) mlp_forward_kernel(const float* __restrict__ params,
                                                                   const float* __restrict__ X, int n,
                                                                   float* __restrict__ y) {
@@ -143,11 +168,14 @@ __global__ void __launch_bounds__(64 * kWaves) mlp_forward_kernel(const float* _
     __shared__ float Y[kWaves][16];
     const int l = threadIdx.x & 63, c = l & 15, g = l >> 4, w = threadIdx.x >> 6;
     const int groups = (n + 15) / 16;
-    for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+    float xa[6];
+    const auto load = [&](int base) { load_x(X, min(base + c, n - 1), base + c < n, g, xa); };
+    Params P;   // in flight together with the first group's samples
+    P.fetch(params);
+    load(blockIdx.x * 16);
+    P.store(S);
+    for (int grp = blockIdx.x;;) {
         const int base = grp * 16;
-        float xa[6];
-        load_x(X, base + c < n ? base + c : -1, g, xa);
-        if (grp == (int)blockIdx.x) load_params(S, params);
         __syncthreads();   // the parameters; H of the previous group is no longer read
         layer1(S, xa, H, w, c, g);
         __syncthreads();
@@ -160,6 +188,9 @@ __global__ void __launch_bounds__(64 * kWaves) mlp_forward_kernel(const float* _
         __syncthreads();
         const int s = threadIdx.x;
         if (s < 16 && base + s < n) y[base + s] = ((Y[0][s] + Y[1][s]) + (Y[2][s] + Y[3][s])) + S.b3;
+        grp += gridDim.x;
+        if (grp >= groups) break;
+        load(grp * 16);
     }
 }
 
@@ -181,16 +212,26 @@ __global__ void __launch_bounds__(64 * kWaves) mlp_grad_kernel(const float* __re
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 dW2[4] = {zero, zero, zero, zero}, dW1[2] = {zero, zero};
     float gB1 = 0.0f, gB2 = 0.0f, gW3 = 0.0f, gB3 = 0.0f, sq = 0.0f;
-    for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-        const int base = grp * 16;
-        float xa[6], tg[4];
-        load_x(X, base + c < n ? (idx ? idx[base + c] : base + c) : -1, g, xa);
+    float xa[6], tg[4];
+    const auto load = [&](int base) {
+        int i = min(base + c, n - 1), b[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int b = base + 4 * g + r;
-            tg[r] = b < n ? tgt[idx ? idx[b] : b] : 0.0f;
+        for (int r = 0; r < 4; ++r) b[r] = min(base + 4 * g + r, n - 1);
+        if (idx) {
+            i = idx[i];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) b[r] = idx[b[r]];
         }
-        if (grp == (int)blockIdx.x) load_params(S, params);
+        load_x(X, i, base + c < n, g, xa);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tg[r] = tgt[b[r]];
+    };
+    Params P;   // in flight together with the first group's samples
+    P.fetch(params);
+    load(blockIdx.x * 16);
+    P.store(S);
+    for (int grp = blockIdx.x;;) {
+        const int base = grp * 16;
         __syncthreads();   // the parameters; H and D of the previous group are no longer read
         const f32x4 z1 = layer1(S, xa, H, w, c, g);
         __syncthreads();
@@ -255,7 +296,9 @@ __global__ void __launch_bounds__(64 * kWaves) mlp_grad_kernel(const float* __re
             dW1[0] = mfma4(a, H[(4 * s + g) * kR2 + c], dW1[0]);
             dW1[1] = mfma4(a, c < 8 ? H[(4 * s + g) * kR2 + 16 + c] : 0.0f, dW1[1]);
         }
-        __syncthreads();
+        grp += gridDim.x;
+        if (grp >= groups) break;
+        load(grp * 16);
     }
     float* const out = part + (size_t)blockIdx.x * (kNP + 1);
 #pragma unroll
