@@ -92,85 +92,120 @@ void he_uniform(std::vector<float>& th, uint64_t seed) {
 }
 
 // Workspaces of skel_mlp_grad, kept between calls: allocating and freeing one
-// in stream order took 18 of a 256-sample gradient call's 28 us of host time.  An
-// entry belongs to one call at a time; its event marks the end of the work that
-// used it, and the next user's stream waits for that, whatever stream or thread
-// it is.  At most kMaxEntries entries are held (a gradient needs at most 6 MB);
-// one that kIdleCalls calls in a row did without is freed.
+// in stream order took 18 of a 256-sample gradient call's 28 us of host time.
+// Every entry holds the most a gradient needs (6 MB), so sizes never displace
+// one another, and belongs to one call at a time; its event marks the end of the
+// work that used it, and the next user's stream waits for that, whatever stream
+// or thread it is.  A device has at most kMaxEntries; one that kIdleCalls calls
+// on its device did without is given back.  Entries come and go in the order of
+// the caller's stream (hipMallocAsync, hipFreeAsync): nothing here waits for the
+// device, and nothing is forbidden while another stream is being captured.
 class Workspaces {
   public:
     struct Entry {
-        float* p = nullptr;
-        size_t floats = 0;
-        int device = -1;
-        hipEvent_t done = nullptr;
-        bool busy = false;
-        uint64_t used = 0;
+        float* p;
+        hipEvent_t done;
+        hipStream_t last;   // compared only: which entry to prefer
+        bool busy;
+        uint64_t used;
     };
-    // An entry of at least `floats` floats that `s` may write, or null: the
-    // caller then allocates for itself.
-    Entry* take(int device, size_t floats, hipStream_t s) {
+    // An entry that `s`, a stream of the current device, may write, or null: the
+    // caller then allocates for itself.  A stream keeps to the entry it used last,
+    // so that streams do not wait for one another.
+    Entry* take(int device, hipStream_t s) {
+        if (device < 0 || device >= kMaxDevices) return nullptr;
         std::lock_guard<std::mutex> lock(mu_);
-        ++calls_;
-        Entry* best = nullptr;
-        Entry* spare = nullptr;
-        for (Entry& e : e_) {
+        const uint64_t now = ++calls_[device];
+        Entry *own = nullptr, *spare = nullptr;
+        for (Entry& e : e_[device]) {
             if (e.busy) continue;
-            if (e.p && calls_ - e.used > kIdleCalls && hipEventQuery(e.done) == hipSuccess) drop(e);
-            if (!e.p) {
+            if (e.p && e.last != s && now - e.used > kIdleCalls) drop(e, s);
+            if (!e.p)
                 spare = &e;
-            } else if (e.device == device && e.floats >= floats) {
-                const bool ready = hipEventQuery(e.done) == hipSuccess;
-                if (!best || ready) best = &e;
-                if (ready) break;
-            }
+            else if (e.last == s)
+                own = &e;
         }
-        (void)hipGetLastError();   // a query of work in flight is no error
-        if (best && (!spare || hipEventQuery(best->done) == hipSuccess)) {
-            if (hipStreamWaitEvent(s, best->done, 0) != hipSuccess) return nullptr;
-        } else if (spare) {
-            best = spare;
-            if (hipMalloc((void**)&best->p, sizeof(float) * floats) != hipSuccess) best->p = nullptr;
-            if (best->p && hipEventCreateWithFlags(&best->done, hipEventDisableTiming) != hipSuccess) {
-                (void)hipFree(best->p);
-                best->p = nullptr;
+        Entry* const e = own ? own : spare;
+        if (!e) return nullptr;
+        if (own) {
+            if (hipStreamWaitEvent(s, e->done, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                return nullptr;
             }
-            (void)hipGetLastError();
-            if (!best->p) return nullptr;
-            best->floats = floats;
-            best->device = device;
-        } else {
+        } else if (!fill(*e, s)) {
             return nullptr;
         }
-        best->busy = true;
-        best->used = calls_;
-        return best;
+        e->busy = true;
+        e->last = s;
+        e->used = now;
+        return e;
     }
     // Marks the end of the call's work on s.
-    hipError_t give(Entry* e, hipStream_t s) {
-        const hipError_t r = hipEventRecord(e->done, s);
-        if (r != hipSuccess) (void)hipStreamSynchronize(s);
+    void give(Entry* e, hipStream_t s) {
+        const bool marked = hipEventRecord(e->done, s) == hipSuccess;
         std::lock_guard<std::mutex> lock(mu_);
+        if (!marked) {   // in stream order the memory can still go back, or stay taken for good
+            (void)hipGetLastError();
+            if (!release(*e, s)) return;
+        }
         e->busy = false;
-        return r;
     }
 
   private:
-    static constexpr int kMaxEntries = 4;
+    static constexpr int kMaxDevices = 64, kMaxEntries = 4;
     static constexpr uint64_t kIdleCalls = 256;
-    void drop(Entry& e) {
-        (void)hipEventDestroy(e.done);
-        (void)hipFree(e.p);
+    static bool fill(Entry& e, hipStream_t s) {
+        const size_t bytes = sizeof(float) * mlp_grad_work_floats(1 << 30);
         e = Entry{};
+        if (hipEventCreateWithFlags(&e.done, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            e.done = nullptr;
+            return false;
+        }
+        if (hipMallocAsync((void**)&e.p, bytes, s) == hipSuccess) return true;
+        (void)hipGetLastError();
+        (void)hipEventDestroy(e.done);
+        e = Entry{};
+        return false;
+    }
+    // Frees the entry in s's order; it stays as it is where that is refused.
+    static bool release(Entry& e, hipStream_t s) {
+        if (hipFreeAsync(e.p, s) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        (void)hipEventDestroy(e.done);
+        const bool busy = e.busy;
+        e = Entry{};
+        e.busy = busy;
+        return true;
+    }
+    static void drop(Entry& e, hipStream_t s) {
+        if (hipStreamWaitEvent(s, e.done, 0) == hipSuccess)
+            (void)release(e, s);
+        else
+            (void)hipGetLastError();
     }
     std::mutex mu_;
-    Entry e_[kMaxEntries];
-    uint64_t calls_ = 0;
+    Entry e_[kMaxDevices][kMaxEntries] = {};
+    uint64_t calls_[kMaxDevices] = {};
 };
 
-Workspaces& workspaces() {
-    static Workspaces* const w = new Workspaces();   // never destroyed: the runtime may be gone first
-    return *w;
+Workspaces g_workspaces;   // holds device memory until the process ends
+
+// The device of s if the kept workspaces serve it: it is the current one, and s is
+// not being captured (a captured stream cannot wait for an event recorded outside
+// its graph, which allocates for itself); else -1.
+int workspace_device(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int device = 0;
+    hipDevice_t own = 0;
+    if (hipGetDevice(&device) == hipSuccess && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+        cap == hipStreamCaptureStatusNone && (!s || hipStreamGetDevice(s, &own) == hipSuccess) &&
+        (!s || own == device))
+        return device;
+    (void)hipGetLastError();
+    return -1;
 }
 
 }  // namespace
@@ -189,23 +224,14 @@ extern "C" skel_status skel_mlp_grad(const float* params, const float* X, const 
     clear_error();
     if (n <= 0 || !params || !X || !t || !grad) return set_error(SKEL_EINVAL, "bad MLP gradient arguments");
     const hipStream_t s = (hipStream_t)stream;
-    const size_t floats = mlp_grad_work_floats(n);
-    // A stream under capture cannot wait for an event recorded outside it: its
-    // graph allocates for itself, as does a call that finds every entry taken.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int device = 0;
-    HIP_TRY(hipGetDevice(&device));
-    HIP_TRY(hipStreamIsCapturing(s, &cap));
-    Workspaces::Entry* const ws =
-        cap == hipStreamCaptureStatusNone ? workspaces().take(device, floats, s) : nullptr;
+    Workspaces::Entry* const ws = g_workspaces.take(workspace_device(s), s);
     hipError_t e;
     if (ws) {
         e = launch_mlp_grad(params, X, t, n, grad, loss, ws->p, s);
-        const hipError_t eg = workspaces().give(ws, s);
-        if (e == hipSuccess) e = eg;
+        g_workspaces.give(ws, s);
     } else {
         float* work = nullptr;
-        HIP_TRY(hipMallocAsync((void**)&work, sizeof(float) * floats, s));
+        HIP_TRY(hipMallocAsync((void**)&work, sizeof(float) * mlp_grad_work_floats(n), s));
         e = launch_mlp_grad(params, X, t, n, grad, loss, work, s);
         const hipError_t ef = hipFreeAsync(work, s);
         if (e == hipSuccess) e = ef;

@@ -128,6 +128,43 @@ def test_gradients_on_several_streams_and_threads():
         assert len(got[k]) == 12 and all(torch.equal(g, w) for g in got[k]), k
 
 
+def test_gradients_beside_a_capture_of_another_stream():
+    """While one stream is under a global-mode capture, gradients on other streams run as ever: with the
+    workspaces there are, with one more stream than before and after hundreds of calls on one of them
+    (workspaces come and go), and the captured graph replays with the eager results."""
+    X, t, theta = batch(800, 20000)
+    dX, dt, dth = dev(X), dev(t), dev(theta)
+    y, eager = torch.empty(1000, device="cuda"), torch.empty(1000, device="cuda")
+    sk.mlp_forward(dth, dX[:1000], eager)
+    sizes = (20000, 16, 20000, 300)
+    want = [torch.empty(5825, device="cuda") for _ in sizes]
+    got = [torch.empty(5825, device="cuda") for _ in sizes]
+    loss = [torch.empty(1, device="cuda") for _ in sizes]
+    for w, L, n in zip(want, loss, sizes):
+        sk.mlp_grad(dth, dX[:n], dt[:n], w, L)
+    streams = [torch.cuda.Stream() for _ in sizes]
+    cap, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(cap):
+        graph.capture_begin(capture_error_mode="global")
+        sk.mlp_forward(dth, dX[:1000], y)
+        for s, g, L, n in zip(streams, got, loss, sizes):
+            sk.mlp_grad(dth, dX[:n], dt[:n], g, L, stream=s)
+        for _ in range(300):
+            sk.mlp_grad(dth, dX[:16], dt[:16], got[1], loss[1], stream=streams[1])
+        sk.mlp_grad(dth, dX[:300], dt[:300], got[3], loss[3], stream=streams[3])
+        graph.capture_end()
+    torch.cuda.synchronize()
+    for g, w, n in zip(got, want, sizes):
+        assert torch.equal(g, w), n
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        sk.mlp_grad(dth, dX[:300], dt[:300], got[0], loss[0])
+        torch.cuda.synchronize()
+        assert torch.equal(y, eager) and torch.equal(got[0], want[3])
+
+
 def test_adam_step_elementwise():
     """One Adam step from the same fp32 gradient, at steps 1, 2 and 50: every
     first and second moment within 1e-6 of the block's largest value, and
