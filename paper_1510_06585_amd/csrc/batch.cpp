@@ -189,7 +189,9 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
     A.pre = K.img.pre;
     A.post = K.img.post;
     const int wg = K.wg;
-    const int max_grid = std::max(1, img_batch_blocks_per_cu(A, wg)) * device_cu_count();
+    int per_cu = std::max(1, img_batch_blocks_per_cu(A, wg));
+    if (K.blur) per_cu = std::min(per_cu, kStencilWaves * 64 / wg);
+    const int max_grid = per_cu * device_cu_count();
     // Rows per tile: the plan's tile_h when it was given, else kBatchTileRows
     // for every request.  With work-groups taking groups of adjacent tiles,
     // short tiles keep the tail of the work list fine-grained for the cost

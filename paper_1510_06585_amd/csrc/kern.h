@@ -14,6 +14,12 @@ inline int band_count(int64_t W, bool blur) {
     return (int)((W + bw - 1) / bw);
 }
 
+// Wavefronts per CU that stencil launches are laid out for: 4 per SIMD, also where
+// the registers would let a fifth in, whose tiles are shorter and have more halo
+// rows for no more throughput (plain blur, us, tiles for 16 / 20 wavefronts: 8192^2
+// 107.9 / 114.2, 2847 x 4289 19.5 / 21.1; persistent batch of 128 709 / 735).
+constexpr int kStencilWaves = 16;
+
 // Value (non-moving) image stages inside a fused kernel.
 enum : uint8_t { IOP_NONE = 0, IOP_NOISE = 1, IOP_SOL = 2 };
 

@@ -236,9 +236,9 @@ ImgEntries img_entries_lite(int k) {
     return f[k]();
 }
 
-// The kernels of a chain: one specialised for it (exact mirror flags first, then
-// run-time ones), else the interpreter.  The lite kernels take single images of
-// 4 columns or more only (W = 0: a batch).
+// The kernels of a chain: one specialised for it and its mirror flags, else a lite
+// one (run-time flags; single images of 4 columns or more only, W = 0: a batch),
+// else the interpreter.
 static const ImgEntry* find_entry(const OpList& pre, const OpList& post, bool blur, bool hist, int in_flip,
                                   int out_flip, int variant, int W) {
     const int pe = encode_ops(pre), qe = encode_ops(post);
@@ -253,7 +253,6 @@ static const ImgEntry* find_entry(const OpList& pre, const OpList& post, bool bl
         };
         const ImgEntries t = !blur ? img_entries_point() : (hist ? img_entries_blur_hist() : img_entries_blur());
         if (const ImgEntry* e = find(t, fl)) return e;
-        if (const ImgEntry* e = find(t, -1)) return e;
         if (W >= 4)
             for (int k = 0; k < kLiteTables; ++k)
                 if (const ImgEntry* e = find(img_entries_lite(k), -1)) return e;

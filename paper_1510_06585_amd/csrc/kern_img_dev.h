@@ -429,6 +429,19 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
                         st128(v, rout, rowoff + out_vec);
                     else
                         st128<kStream>(v, rout, rowoff + out_vec);
+                } else if constexpr (!I && LITE && PRE != kGeneric) {
+                    // The lane that the row ends in: its first one to three pixels are
+                    // inside (bands start at multiples of 4).  Offsets and conditions are
+                    // formed here: kept over the rows, for either mirror, they were 30
+                    // registers, which most of these kernels do not have left.
+                    int u = ub;
+                    asm("" : "+v"(u));
+                    if (u >= x0 && u < xend) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i)
+                            if (u + i < xend)
+                                st32(fin[i], rout, rowoff + (uint32_t)(V.out_flip ? (W - 1 - u - i) : u + i) * 4u);
+                    }
                 } else if constexpr (!I) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -631,8 +644,14 @@ static __device__ __forceinline__ void write_hist_row(uint32_t* lh, uint32_t* ro
 
 // FL >= 0 fixes the mirror flags at compile time (bit 0: input, bit 1:
 // output), which removes the per-row selects of the flipped data order;
-// FL = -1 reads them from the arguments.
-// Specialised stencil kernels are held to 128 VGPRs, four wavefronts per SIMD.
+// FL = -1 reads them from the arguments (the interpreter and the lite kernels).
+// Specialised stencil kernels are held to 128 VGPRs, four wavefronts per SIMD, and
+// none keeps anything in private memory: the named chains have a kernel for each
+// of the four mirror flags (one reading them took 117-128 registers and, with a
+// histogram, up to 68 bytes a lane; mirrored MapReduce of 1125 x 1799 in 64-row tiles
+// 49.1 us with it, 44.6 without), and the lite kernels form the offsets of a row's
+// last pixels where they are stored (108 bytes a lane before; the same MapReduce of
+// noise, blur, solarise 50.1 -> 46.3).
 template <int PRE, int POST, bool BLUR, bool HIST, int FL, bool LITE = false>
 __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_band_kernel(const ImgGroupArgs A) {
     __shared__ __attribute__((aligned(16))) uint32_t lh[HIST ? 4 * kHistWgChan : 1];
@@ -765,8 +784,8 @@ struct ImgEntry {
 // output address), so those chains need FL 0 and 2 only.
 #define SKEL_IMG_POINT(P, Hh, NAME) SKEL_IMG_ENTRY(P, 0, false, Hh, 0, NAME), SKEL_IMG_ENTRY(P, 0, false, Hh, 2, NAME)
 #define SKEL_IMG_STENCIL(P, Hh, NAME)                                           \
-    SKEL_IMG_ENTRY(P, 0, true, Hh, 0, NAME), SKEL_IMG_ENTRY(P, 0, true, Hh, 2, NAME), \
-        SKEL_IMG_ENTRY(P, 0, true, Hh, -1, NAME)
+    SKEL_IMG_ENTRY(P, 0, true, Hh, 0, NAME), SKEL_IMG_ENTRY(P, 0, true, Hh, 1, NAME), \
+        SKEL_IMG_ENTRY(P, 0, true, Hh, 2, NAME), SKEL_IMG_ENTRY(P, 0, true, Hh, 3, NAME)
 
 // Chains of up to two value stages on either side of a stencil, or on their own
 // (5 = noise twice, 6 = solarise then noise): single images of 4 columns or more.

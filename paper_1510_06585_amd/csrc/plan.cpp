@@ -489,10 +489,13 @@ int device_cu_count() {
 //    oldest wavefronts of a SIMD issue first).  When that gives a round or more,
 //    the height is raised just enough to make the tile count a whole number of
 //    rounds: a few tiles over a round boundary form a tail round of their own.
+//    Rounds of stencil tiles count kStencilWaves per CU, also where more would fit.
 static int fitted_tile_h(const ImgGroupArgs& A, bool blur, bool hist, const Config& c) {
     if (A.W <= 0 || A.H <= 0) return 1;
     if (!blur && !hist) return std::min(3, (int)A.H);
-    const double resident = (double)img_waves_per_cu(A, blur, hist, c.wg, c.variant) * device_cu_count();
+    int waves = img_waves_per_cu(A, blur, hist, c.wg, c.variant);
+    if (blur) waves = std::min(waves, kStencilWaves);
+    const double resident = (double)waves * device_cu_count();
     const int64_t nb = std::max<int32_t>(1, A.nbands);
     const double x = (double)A.H * nb / std::max(1.0, resident);
     if (blur) {

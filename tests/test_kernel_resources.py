@@ -24,7 +24,7 @@ def kernels():
     return out
 
 
-@pytest.mark.parametrize("family", ["mlp_"])
+@pytest.mark.parametrize("family", ["mlp_", "img_band_", "img_batch_", "fft_", "vec_", "nbody_", "gray_", "hist_", "while_"])
 def test_no_private_memory(family):
     found = {n: k for n, k in kernels().items() if family in n}
     assert found
