@@ -38,13 +38,20 @@ struct OpList {
 // only where the input exceeds that cache anyway.
 enum : int32_t { STREAM_NONE = 0, STREAM_OUT = 1, STREAM_BOTH = 2 };
 constexpr int64_t kMallBytes = (int64_t)256 << 20;   // memory-side cache
-// Policy of a kernel that reads in_bytes: `last` when nothing of this plan reads
-// its output.  From three quarters of the cache on, little of an input survives
+// Policy of a kernel that reads in_bytes: `last` when its output is not to be kept
+// for a reader in this plan.  From three quarters of the cache on, little of an input survives
 // until a next run could find it there (fp32 chains with 240 MB of input 5.25 ->
 // 5.58 TB/s, with 120 MB and one stage 6.7 -> 6.0).
 inline int32_t stream_policy(int64_t in_bytes, bool last) {
     return in_bytes >= kMallBytes / 4 * 3 ? STREAM_BOTH : (last ? STREAM_OUT : STREAM_NONE);
 }
+
+// Whether a while Loop's images are stored to stay in the memory-side cache for the
+// next iteration: a mid-size pair does, a large one does not fit beside the loop's
+// input, and a small one is not written faster that way.  Eight iterations of blur5
+// with a histogram, us, stored to stay / streamed: 8 MB 140 / 136, 17 MB 162 / 162,
+// 30 MB 199 / 205, 67 MB 296 / 334, 144 MB 579 / 551.
+inline bool while_keeps(int64_t bytes) { return bytes >= kMallBytes / 12 && bytes < kMallBytes / 8 * 3; }
 
 // One fused image kernel: pre-stages, an optional 5x5 blur, post-stages, an
 // optional histogram/sum epilogue.  The kernel iterates over coordinates u of

@@ -593,13 +593,13 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
         }
         if constexpr ((PRE != 0 && PRE != 2) || (POST != 0 && POST != 2)) {   // a noise stage, or unknown
             if ((W & 3) != 0 && (any_flip(pre) || any_flip(post))) {
-                sweep(inner, by_pixel, keep, stream);
+                sweep(inner, by_pixel, keep, std::integral_constant<int, kByArgs>{});
                 return;
             }
         }
         if (V.stream == STREAM_BOTH)
             sweep(inner, aligned, stream, stream);
-        else if (HIST || V.stream == STREAM_OUT)
+        else if (V.stream == STREAM_OUT)
             sweep(inner, aligned, keep, stream);
         else
             sweep(inner, aligned, keep, keep);

@@ -684,9 +684,10 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             const int64_t chunks = (sh.H + A.tile_h - 1) / A.tile_h;
             A.ntiles = (sh.W == 0 || sh.H == 0) ? 0 : (int32_t)(A.nbands * chunks);
             A.write_out = 1;
-            // An intermediate or a while Loop's image is read by the next kernel,
-            // so only final images are streamed out.
-            A.stream = stream_policy(sh.W * sh.H * 4, K.dst == -2 && !L.is_while && !red_sep);
+            // Intermediates are read by the next kernel, a while Loop's image by the
+            // next iteration: those are kept where that pays.
+            const int64_t bytes = sh.W * sh.H * 4;
+            A.stream = stream_policy(bytes, K.dst == -2 && !red_sep && !(L.is_while && while_keeps(bytes)));
             A.hist_ks = hist_copies_log2(bins, kHistWgWords);
             A.bins = bins;
             K.bins = bins;

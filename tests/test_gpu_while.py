@@ -336,3 +336,27 @@ def test_step_after_one_and_several_merge_chunks(body, H):
         assert_image_equal(args[1].cpu().numpy(), x, f"count {n}")
         assert (args[2].cpu().numpy().view(np.uint32) == rh).all()
         assert (args[3].cpu().numpy().view(np.uint64) == rs).all()
+
+
+@pytest.mark.parametrize("W", [2368, 2369])
+@pytest.mark.parametrize("names", ["blur5", "noise,mirror,solarise,blur5", "noise,blur5,solarise"])
+def test_images_kept_for_the_next_iteration(names, W):
+    """Images of 22 MB, which the loop stores to stay in the memory-side cache (from 256 MB / 12 on):
+    whole bands with aligned and, with a mirrored noise in rows of an odd width, unaligned pixel groups."""
+    H = 2372
+    img = synth.image(W, H, W)
+    assert img.nbytes >= (256 << 20) // 12
+    stages = [(n, {"seed": 3 + i} if n == "noise" else {}) for i, n in enumerate(names.split(","))]
+    x = img
+    for _ in range(2):
+        x, h, s = oracle.run_image_pipeline(x, stages, "hist_sum")
+    root = sk.LoopWhile(sk.image_chain(stages, "hist_sum"), 2, 1, ">=", 0)
+    args = [cuda(img), torch.empty((H, W, 4), dtype=torch.uint8, device="cuda"),
+            torch.zeros((4, 256), dtype=torch.int32, device="cuda"),
+            torch.zeros((4,), dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")]
+    plan = sk.Plan(root, args)
+    plan.run(args)
+    torch.cuda.synchronize()
+    assert int(args[4].item()) == 2
+    assert_image_equal(args[1].cpu().numpy(), x, names)
+    assert (args[2].cpu().numpy().view(np.uint32) == h).all() and (args[3].cpu().numpy().view(np.uint64) == s).all()
