@@ -5,16 +5,15 @@
 // Each lane moves 16 bytes per access; a chain of k stages reads the input
 // and k side vectors once and writes the output once.  A reversal is an
 // address remap: stage inputs are read at u or n-1-u of the kernel's
-// iteration coordinate u.  The sum is formed per thread in fp32, then per
-// wavefront (cross-lane adds) and per work-group (LDS) in fp64; a second kernel
-// adds the work-group partials in a fixed order in fp64.
+// iteration coordinate u.  The sum of a vector of four is formed in fp32, those of
+// a thread, a wavefront (cross-lane adds) and a work-group (LDS) in fp64; a second
+// kernel adds the work-group partials in a fixed order in fp64.
 #include "kern_common.h"
 #include "kern.h"
 
 namespace skel {
 
-static __device__ __forceinline__ double wave_sum(float x) {
-    double v = x;
+static __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
@@ -32,7 +31,7 @@ __global__ void __launch_bounds__(1024) vec_chain_kernel(const VecGroupArgs A) {
     const __amdgpu_buffer_rsrc_t rout = mk_rsrc(A.out, nbytes);
     const int64_t nvec = (n + 3) / 4;
     const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
-    float acc = 0.0f;
+    double acc = 0.0;
     for (int e = 0; e < A.ept; ++e) {
         const int64_t v = (int64_t)e * nthreads + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
         if (v >= nvec) break;
@@ -77,7 +76,7 @@ __global__ void __launch_bounds__(1024) vec_chain_kernel(const VecGroupArgs A) {
             for (int i = 0; i < 4; ++i) x[i] = __builtin_fmaf(a, x[i], w[i]);
         }
         if (fullv) {
-            acc += (x[0] + x[1]) + (x[2] + x[3]);
+            acc += (double)((x[0] + x[1]) + (x[2] + x[3]));
             if (A.write_out) {
                 u32x4 r;
                 if (A.out_flip) {
@@ -94,7 +93,7 @@ __global__ void __launch_bounds__(1024) vec_chain_kernel(const VecGroupArgs A) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (u0 + i < n) {
-                    acc += x[i];
+                    acc += (double)x[i];
                     if (A.write_out) {
                         const int64_t dst = A.out_flip ? (n - 1 - (u0 + i)) : (u0 + i);
                         st32(__float_as_uint(x[i]), rout, (uint32_t)(dst * 4));
@@ -105,12 +104,11 @@ __global__ void __launch_bounds__(1024) vec_chain_kernel(const VecGroupArgs A) {
     }
     if (A.partials == nullptr) return;
     // Reduce: wavefront, then work-group (fixed order); the work-group's
-    // partial is stored, and vec_sum_merge_kernel adds the partials.  Beyond a
-    // lane's own elements the adds are in fp64 and a partial is rounded once, so
-    // that wider groups lose no accuracy: error over the vector's norm, rms of 1000
-    // to 5e7 elements, 256-lane groups in fp32 1.06e-7, 1024-lane groups in fp32
-    // 1.20e-7, this form 6.4e-8; 5e7
-    // elements 129.1 us before, 129.4 after.
+    // partial is stored, and vec_sum_merge_kernel adds the partials.  The adds are in
+    // fp64 and a partial is rounded once, so that neither wider groups nor more
+    // vectors per thread lose accuracy: error over the vector's norm, rms of 1000 to
+    // 5e7 elements, 256-lane groups in fp32 1.03e-7, 1024-lane groups in fp32
+    // 1.20e-7, fp64 beyond a vector's four 6.3e-8, at no more time (5e7: 128.2 us).
     const double wacc = wave_sum(acc);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) wsum[wave] = wacc;

@@ -349,14 +349,21 @@ skel_status resolve_config(const Linear& L, const Shape& sh, const skel_plan_opt
         if (c.tile_h < 1 || c.tile_h > kMaxDim) return set_error(SKEL_EINVAL, "tile_h out of range");
         c.ept = 1;
     } else if (L.dom == DOM_F32) {
-        // One vector per thread (10^7 elements: 6.7 TB/s, 4 vectors 6.3; with a sum
-        // 32.9 us against 36.9), in 1024-lane groups from 2^20 vectors on (8x10^6
-        // with a sum: 25.4 us, 256 lanes 26.5).  Sums of 2^23 vectors or more take
-        // 4 per thread, for fewer partials (32x10^6: 84.5 us, one vector 87.6).
+        // One vector per thread (10^7 elements: 6.7 TB/s, 4 vectors 6.3), in 1024-lane
+        // groups from 2^20 vectors on.  Sums take 4 per thread there, which leaves a
+        // quarter of the partials and of the reductions across lanes (1024 lanes, us,
+        // 1 / 4 vectors: a sum on its own of 4.2x10^6 8.0 / 7.3, of 32x10^6 46.3 / 40.1;
+        // saxpy and sum in a kernel each, 32x10^6, 100.0 / 87.6; both in one 65.5 / 63.2).
+        // Fused chains of several saxpy stages, whose threads then hold more loads than
+        // they have registers for, do so from 6x10^6 elements (4.2x10^6, four stages: 18.6 /
+        // 19.5; 8x10^6 30.4 / 29.9).
         const int64_t nvec = (sh.n + 3) / 4;
+        int nops = 0;
+        for (const Stage& s : L.st) nops += s.op == SKEL_OP_SAXPY;
+        const bool few = c.fusion == SKEL_FUSE_ON && nops > 1 && nops <= kMaxVecOps && nvec < ((int64_t)3 << 19);
         c.wg = o->wg ? o->wg : (nvec >= ((int64_t)1 << 20) ? 1024 : 256);
         if (c.wg < 64 || c.wg > 1024 || c.wg % 64) return set_error(SKEL_EINVAL, "wg must be a multiple of 64 up to 1024");
-        c.ept = o->ept ? o->ept : (L.red >= 0 && nvec >= ((int64_t)1 << 23) ? 4 : 1);
+        c.ept = o->ept ? o->ept : (L.red >= 0 && nvec >= ((int64_t)1 << 20) && !few ? 4 : 1);
         if (c.ept < 1 || c.ept > 64) return set_error(SKEL_EINVAL, "ept out of range");
         c.tile_h = 0;
     } else if (L.dom == DOM_GRAY) {

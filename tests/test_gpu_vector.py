@@ -154,3 +154,19 @@ def test_sum_keeps_ones_beside_a_cancelling_pair(n, far):
     assert float(np.float32(ones)) == ones
     _, s = run_chain([("saxpy", {"a": 1.0})], v, [np.zeros(n, np.float32)], "sum")
     assert s == ones
+
+
+@pytest.mark.parametrize("options", [None, {"wg": 64}, {"ept": 64, "wg": 256}])
+def test_sum_keeps_ones_in_the_lane_of_a_cancelling_pair(options):
+    """+2^26 and -2^26 in two of one lane's vectors, the other elements ones: the lane adds its vectors'
+    sums in fp64, so none of those between the two is rounded off and every partial is a whole number
+    below 2^24."""
+    n = 1 << 25
+    v = np.ones(n, np.float32)
+    ept = (options or {}).get("ept", 4)
+    far = n // ept * (ept - 1)   # the first lane's last vector
+    v[0:4] = v[far:far + 4] = 0.0
+    ones = int(v.sum(dtype=np.float64))
+    v[0], v[far] = 2.0 ** 26, -2.0 ** 26
+    _, s = run_chain([("saxpy", {"a": 1.0})], v, [np.zeros(n, np.float32)], "sum", options)
+    assert float(np.float32(ones)) == ones and s == ones

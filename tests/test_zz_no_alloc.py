@@ -172,3 +172,28 @@ def test_histogram_rows_at_the_scratch_limit(H, W, options, fits):
     for r, g in zip(ref, _host(a)):
         assert (r == g).all()
     plan.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("options,fits", [({"wg": 64}, True), ({"wg": 128}, True), ({}, True),
+                                          ({"wg": 64, "ept": 1}, False)])
+def test_partials_at_the_scratch_limit(options, fits):
+    """A scratch vector 64 KB short of the limit and the partial sums of a work-group size that was
+    asked for: with the default of 4 vectors per lane they fit (64 lanes: 32 KB), with 1 they do not."""
+    n = 4 * ((1 << 21) - 4096)
+    root = sk.image_chain([("saxpy", {"a": 1.5}), ("saxpy", {"a": -0.5})], "sum")
+    args = [torch.rand(n, device="cuda") for _ in range(3)] + [torch.empty(n, device="cuda"),
+                                                               torch.zeros(1, device="cuda")]
+    plan = sk.Plan(root, args, {"fusion": sk.FUSE_OFF, **options})
+    plan.run(args)
+    ref = _host(args)[2:]
+    args[3].fill_(0)
+    if fits:
+        plan.run_noalloc(args)
+        got = _host(args)[2:]
+        assert (ref[0] == got[0]).all() and ref[1] == got[1]
+    else:
+        with pytest.raises(sk.SkelError) as e:
+            plan.run_noalloc(args)
+        assert e.value.status == sk.EUNSUPPORTED
+    plan.destroy()
