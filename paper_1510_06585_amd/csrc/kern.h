@@ -19,6 +19,9 @@ inline int band_count(int64_t W, bool blur) {
 // rows for no more throughput (plain blur, us, tiles for 16 / 20 wavefronts: 8192^2
 // 107.9 / 114.2, 2847 x 4289 19.5 / 21.1; persistent batch of 128 709 / 735).
 constexpr int kStencilWaves = 16;
+// Work-groups with a histogram that fit a CU's LDS: 32 KB each in allocation units of
+// 1280 bytes, which the occupancy query (5 groups) leaves out.
+constexpr int kHistGroups = 4;
 
 // Value (non-moving) image stages inside a fused kernel.
 enum : uint8_t { IOP_NONE = 0, IOP_NOISE = 1, IOP_SOL = 2 };

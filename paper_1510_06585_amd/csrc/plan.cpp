@@ -483,31 +483,59 @@ int device_cu_count() {
 //    loads at once and ends without waiting for its stores; in a longer tile the
 //    in-order counter of vector memory makes every load also wait for the stores
 //    before it (8192 x 8192 / 8700 x 8192 / 4289 x 2847, TB/s: 2 rows 6.2 / 5.8 / 5.2, 3 rows
-//    6.0 / 6.2 / 5.5, 4 rows 5.1 / 4.8 / 5.4, 16 rows 5.1 / 5.1 / 5.1).
+//    6.0 / 6.2 / 5.5, 4 rows 5.1 / 4.8 / 5.4, 16 rows 5.1 / 5.1 / 5.1).  Fewer where that
+//    leaves less than 2048 tiles, 2 wavefronts per SIMD (noise, solarise, mirror of
+//    1000 x 1001, us: 2 rows 4.1, 3 rows 4.5).
+//  - The interpreter without a histogram is slower over a row than its memory: whole
+//    groups of 4 rows, whose loop shares the stage lists, where these still fill
+//    most of a round, else single rows (noise, solarise, noise, us, 1 / 3 / 4 rows:
+//    1125 x 1799 8.5 / 8.9 / 9.6, 2000^2 13.0 / 13.5 / 11.7, 8192^2 168 / 135 / 124).
 //  - Stencil tiles of large images (x >= 10): one round, x rounded up, for the
 //    fewest halo rows (8192^2 with a histogram: 69 rows 4400 GB/s, 50 rows 4240;
 //    4289 x 2847: 13 rows 2980, 8 rows 2570).
 //  - Stencil tiles of smaller images: half a round, two work-groups on every CU;
 //    a few tiles more, and some CUs run a third (fused chain, us: 2048^2 10 rows
 //    12.1, 8 rows 13.4; 1000 x 4000 10 rows 11.9, 9 rows 14.5; 1799 x 1125 5 rows
-//    8.7, 6 rows 9.0).
+//    8.7, 6 rows 9.0).  Work-groups of 64 or 128 lanes with a histogram, 4 or 8
+//    wavefronts a CU: a whole round or three quarters (1125 x 1799, 128 lanes: 6 rows
+//    17.2, 9 rows 19.2).
+//  - Where half a round is tiles of at most 3 rows, which load 7, a quarter: one
+//    work-group on every CU (1000 x 1001, us: 5 rows 6.2, 3 rows 6.8; 700^2 3 rows
+//    4.6, 2 rows 5.5); with longer stage lists, which a second wavefront per SIMD
+//    hides less, at most 2 rows (noise, blur, noise, solarise, noise of 1000 x 1001:
+//    5 rows 14.8, 3 rows 13.8).
+//  - Rounds of stencil tiles count kStencilWaves per CU, also where more would fit,
+//    and with a histogram kHistGroups work-groups (64 lanes, 8192^2: 222-row tiles, a
+//    round of 5 groups, 296 us, 273 rows 162).
 //  - Otherwise 3 sqrt(x) rows for reduce tiles (at least 2): taller tiles amortise
 //    the histogram's clear and row store, shorter ones leave a shorter tail (the
 //    oldest wavefronts of a SIMD issue first).  When that gives a round or more,
 //    the height is raised just enough to make the tile count a whole number of
 //    rounds: a few tiles over a round boundary form a tail round of their own.
-//    Rounds of stencil tiles count kStencilWaves per CU, also where more would fit.
 static int fitted_tile_h(const ImgGroupArgs& A, bool blur, bool hist, const Config& c) {
     if (A.W <= 0 || A.H <= 0) return 1;
-    if (!blur && !hist) return std::min(3, (int)A.H);
+    const int64_t nb = std::max<int32_t>(1, A.nbands);
+    if (!blur && !hist) {
+        const int64_t rows = nb * A.H;
+        if (!strcmp(img_kernel_name(A, blur, hist, c.variant), "img_generic"))
+            return (int)std::min<int64_t>(rows >= 15 * 1024 ? 4 : 1, A.H);
+        return (int)std::min<int64_t>({std::max<int64_t>(1, (rows + 2047) / 2048), 3, A.H});
+    }
     int waves = img_waves_per_cu(A, blur, hist, c.wg, c.variant);
     if (blur) waves = std::min(waves, kStencilWaves);
+    if (blur && hist) waves = std::min(waves, kHistGroups * c.wg / 64);
     const double resident = (double)waves * device_cu_count();
-    const int64_t nb = std::max<int32_t>(1, A.nbands);
     const double x = (double)A.H * nb / std::max(1.0, resident);
     if (blur) {
-        const int64_t chunks = std::max<int64_t>(1, (int64_t)(x >= 10.0 ? resident : resident / 2) / nb);
-        return (int)std::min<int64_t>(std::max<int64_t>(2, (A.H + chunks - 1) / chunks), A.H);
+        const auto rows = [&](double tiles) {
+            const int64_t chunks = std::max<int64_t>(1, (int64_t)tiles / nb);
+            return std::min<int64_t>(std::max<int64_t>(2, (A.H + chunks - 1) / chunks), A.H);
+        };
+        if (x >= 10.0 || waves <= 4) return (int)rows(resident);
+        if (waves <= 8) return (int)rows(resident * 0.75);
+        const int64_t half = rows(resident / 2);
+        const bool light = A.pre.n <= 2 && A.post.n <= 2;
+        return (int)(half <= (light ? 3 : 2) ? rows(resident / 4) : half);
     }
     int th = std::max(2, (int)std::lround(3.0 * std::sqrt(x)));
     const double rounds = (double)nb * ((A.H + th - 1) / th) / std::max(1.0, resident);

@@ -358,3 +358,25 @@ def test_while_loop_option_rejections():
     for kw in ({"carried_mask": 0b1111}, {"kind": "delta", "check_every": -1}):
         sk.LoopWhile(body, 3, 0, ">", 0, **kw)
     sk.LoopWhile(body_sum, 3, 0, ">", 0, carried_mask=0b111)
+
+
+@pytest.mark.parametrize("names,reduce,H,W,wg,rows", [
+    ("noise,solarise,blur5,mirror", "hist_sum", 8192, 8192, 64, 274),    # a round of 4 groups per CU: 30 x 34 tiles
+    ("noise,solarise,blur5,mirror", "hist_sum", 8192, 8192, 256, 69),    # 120 x 34 tiles of 4096
+    ("noise,solarise,blur5,mirror", "hist_sum", 1125, 1799, 256, 5),     # half a round
+    ("noise,solarise,blur5,mirror", "hist_sum", 1125, 1799, 128, 6),     # three quarters of a round of 8 wavefronts
+    ("noise,solarise,blur5,mirror", None, 1000, 1001, 256, 5),           # a quarter: half would be 3 rows
+    ("noise,blur5,noise,solarise,noise", None, 1000, 1001, 256, 3),
+    ("noise,solarise,mirror", None, 1000, 1001, 256, 2),
+    ("noise,solarise,mirror", None, 256, 512, 256, 1),
+    ("noise,solarise,mirror", None, 2847, 4289, 256, 3),
+    ("noise,solarise,noise", None, 1125, 1799, 256, 1),                  # interpreted
+    ("noise,solarise,noise", None, 2000, 2000, 256, 4)])
+def test_default_tile_rows(names, reduce, H, W, wg, rows):
+    stages = [(n, {"seed": 1} if n == "noise" else {}) for n in names.split(",")]
+    args = [sk.proto([H, W, 4], sk.U8)] * 2
+    if reduce:
+        args += [sk.proto([4, 256], sk.U32), sk.proto([4], sk.U64)]
+    plan = sk.Plan(sk.image_chain(stages, reduce), args, {"wg": wg})
+    assert plan.describe()["kernels"][0]["tile_h"] == rows
+    plan.destroy()
