@@ -527,18 +527,24 @@ skel_status noalloc_prepare(skel_plan p, const skel_buffer* args, int32_t nargs,
                 off += align256(sizeof(uint32_t) * 4 * (size_t)k.bins * (size_t)std::max(1, k.grid));
             }
     }
-    if (off > cap && L.has_hrows) {
+    if (off > cap && L.has_hrows && p->kernels.back().blur) {
+        // Taller tiles, down to the rows there is room for: default tiles need no more
+        // than the cap leaves, given ones what noalloc_max_groups says.  Its bands may be
+        // fewer than the tiles of one chunk; those few rows go to the spare ones.
         const Kernel& k = p->kernels.back();   // the reduce comes last
-        const int64_t most = k.reduce && k.blur ? noalloc_max_groups(k, p->cfg) : k.grid;
-        const auto end = [&](int64_t groups) {
-            return L.off_hrows + align256(sizeof(uint32_t) * 4 * (size_t)k.bins * (size_t)std::max<int64_t>(1, groups));
-        };
-        if (most < k.grid && end(most) <= cap)
-            for (int t = k.img.tile_h + 1; t <= k.img.H && !L.tile_h; ++t)
-                if (tile_groups(k, t) <= most) {
-                    L.tile_h = t;
-                    off = end(tile_groups(k, t));
-                }
+        const int64_t row = sizeof(uint32_t) * 4 * (int64_t)k.bins;
+        const int64_t room = L.off_hrows <= cap ? (int64_t)(cap - L.off_hrows) / row : 0;
+        const int64_t most = p->cfg.auto_tile ? room : noalloc_max_groups(k, p->cfg);
+        if (most > 0 && most <= room) {
+            int t = std::min(k.img.tile_h + 1, k.img.H);
+            while (t < k.img.H && tile_groups(k, t) > most) ++t;
+            const int64_t groups = tile_groups(k, t);
+            if (groups <= most + (p->cfg.auto_tile ? 0 : kNoallocSpareRows)) {
+                L.tile_h = t;
+                L.total = L.off_hrows + (size_t)(groups * row);
+                return SKEL_OK;
+            }
+        }
     }
     L.total = off;
     if (off > cap)

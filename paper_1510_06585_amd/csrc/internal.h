@@ -112,10 +112,10 @@ skel_status resolve_config(const Linear& lin, const Shape& sh, const skel_plan_o
 // is not valid for this chain (e.g. two stencils forced into one kernel).
 skel_status build_kernels(const Linear& lin, const Shape& sh, const Config& cfg, std::vector<Kernel>& ks);
 // Work-groups, one histogram row each, up to which an allocation-free run makes
-// room for a stencil kernel with a histogram: those of bands of 252 pixels and
-// default tiles of 4 sqrt(x) rows, the sizes by which that entry point accepts a
-// plan.  Where the 248-pixel bands and the default tiles need more groups than
-// that and the rows no longer fit, the run takes taller tiles.
+// room for a stencil kernel with a histogram and tiles of a given height: those of
+// bands of 252 pixels, by which that entry point accepts a plan.  Where the 248-pixel
+// bands need more groups than that and the rows no longer fit, the run takes taller
+// tiles.
 int64_t noalloc_max_groups(const Kernel& K, const Config& cfg);
 // The partition-validity predicate (Sec. 3.1 constraints, adapted): true when
 // the configuration is admissible for this chain and shape.
@@ -180,7 +180,12 @@ struct NoallocLayout {
     size_t total = 0;
 };
 // Checks the arguments as skel_plan_run does, then lays out the plan's scratch;
-// SKEL_EUNSUPPORTED if the plan needs other resources or more than cap bytes.
+// SKEL_EUNSUPPORTED if the plan needs other resources or more than cap bytes.  The
+// region holds kNoallocSpareRows histogram rows more: images of up to 65536 columns
+// have at most 5 more bands of 248 pixels than of 252, which is what a plan that fits
+// with one chunk of the latter can lack.
+constexpr int kNoallocSpareRows = 5;
+constexpr size_t kNoallocSpareBytes = (size_t)kNoallocSpareRows * 4 * 256 * sizeof(uint32_t);
 skel_status noalloc_prepare(skel_plan p, const skel_buffer* args, int32_t nargs, size_t cap, NoallocLayout& L);
 // Enqueues the plan's kernels with its scratch in `region` (device memory of
 // at least L.total bytes); the plan's own scratch pointers are left as they were.

@@ -17,7 +17,7 @@
 
 using namespace skel;
 
-static __device__ __align__(256) unsigned char scratch[SKEL_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[SKEL_NOALLOC_SCRATCH_BYTES + kNoallocSpareBytes];
 
 namespace {
 

@@ -547,22 +547,10 @@ static int fitted_tile_h(const ImgGroupArgs& A, bool blur, bool hist, const Conf
 }
 
 int64_t noalloc_max_groups(const Kernel& K, const Config& c) {
-    const ImgGroupArgs& A = K.img;
-    const int64_t nb = (A.W + 251) / 252;
-    int64_t th = c.tile_h;
-    if (c.auto_tile) {
-        const double resident =
-            std::max(1.0, (double)img_waves_per_cu(A, true, true, c.wg, c.variant) * device_cu_count());
-        th = std::max<int64_t>(2, std::lround(4.0 * std::sqrt((double)A.H * nb / resident)));
-        const double rounds = (double)nb * ((A.H + th - 1) / th) / resident;
-        if (rounds >= 1.0) {
-            const int64_t chunks = std::max<int64_t>(1, (int64_t)(std::lround(rounds) * resident) / nb);
-            th = std::max<int64_t>(2, (A.H + chunks - 1) / chunks);
-        }
-    }
-    th = std::max<int64_t>(1, std::min<int64_t>(th, A.H));
+    const int64_t th = std::max<int64_t>(1, std::min<int64_t>(c.tile_h, K.img.H));
+    const int64_t tiles = ((K.img.W + 251) / 252) * ((K.img.H + th - 1) / th);
     const int waves = c.wg / 64;
-    return (nb * ((A.H + th - 1) / th) + waves - 1) / waves;
+    return (tiles + waves - 1) / waves;
 }
 
 skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std::vector<Kernel>& ks) {

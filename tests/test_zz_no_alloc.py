@@ -197,3 +197,23 @@ def test_partials_at_the_scratch_limit(options, fits):
             plan.run_noalloc(args)
         assert e.value.status == sk.EUNSUPPORTED
     plan.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,W,options", [(1982, 2000, {}), (16775, 250, {"tile_h": 16775, "wg": 64}),
+                                         (16775, 250, {"tile_h": 20000, "wg": 64})])
+def test_two_scratch_images_and_histogram_rows_at_the_limit(H, W, options):
+    """Three stencil kernels, two scratch images of almost 16 MB each: default tiles leave room for fewer
+    rows than they would take (the chain's last kernel has 16 wavefronts per CU where 12 were counted
+    once), and one band of 252 pixels, whose row just fits, is two of 248."""
+    img = synth.image(H, H, W)
+    stages = [("blur5", {}), ("blur5", {}), ("blur5", {}), ("noise", {"seed": 3})]
+    a, b = _image_args(img, "hist_sum"), _image_args(img, "hist_sum")
+    plan = sk.Plan(sk.image_chain(stages, "hist_sum"), a, options)
+    plan.run(a)
+    ref, d = _host(a), plan.describe()
+    plan.run_noalloc(b)
+    for r, g in zip(ref, _host(b)):
+        assert (r == g).all()
+    assert plan.describe() == d
+    plan.destroy()
