@@ -345,9 +345,11 @@ skel_status skel_plan_describe(skel_plan plan, char* buf, size_t len);
  * hipEventElapsedTime.  Image kernels take both timestamps from their own
  * dispatch (hipExtLaunchKernel), which brackets the kernel's execution
  * exactly; other kernels have the events recorded on the stream immediately
- * before and after the launch.  kernel < 0 or NULL events clear the hook.  Not
- * applied inside captured graphs (N-body loops, batched runs).  The caller
- * owns the events. */
+ * before and after the launch; FFT batches of more than 280 transforms run in
+ * equal parts of at most that many, and the events bracket the first part's
+ * launch (skel_plan_describe gives its grid).  kernel < 0 or NULL events clear
+ * the hook.  Not applied inside captured graphs (N-body loops, batched runs).
+ * The caller owns the events. */
 skel_status skel_plan_kernel_events(skel_plan plan, int32_t kernel, void* start, void* end);
 
 /* Frees the plan and everything it owns; waits for none of its work (the

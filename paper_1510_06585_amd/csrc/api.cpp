@@ -292,19 +292,12 @@ skel_status run_gray(skel_plan p, const skel_buffer* args, hipStream_t s) {
     return SKEL_OK;
 }
 
-// A batch runs in equal parts of at most kFftRun transforms, each through all
-// passes, so that a part's intermediates (0.54 MB a transform, twice) are still
-// partly in the memory-side cache when the next pass reads them: 300 transforms
-// 188 -> 179 us, 384: 231 -> 223, 450: 274 -> 260, 512: 318 -> 297; parts of 128 lose
-// that again to the launches.  A measured kernel runs in one part.
-constexpr int64_t kFftRun = 256;
-
 skel_status run_fft(skel_plan p, const skel_buffer* args, hipStream_t s) {
     const int64_t B = p->sh.n;
-    const int64_t parts = p->prof_kernel >= 0 ? 1 : std::max<int64_t>(1, (B + kFftRun - 1) / kFftRun);
-    const int64_t part = std::max<int64_t>(1, (B + parts - 1) / parts);
+    const int64_t part = std::max<int64_t>(1, fft_part(B));
     constexpr size_t kBytes = (size_t)kFftPoints * 2 * sizeof(float);
-    for (int64_t b = 0; b < B; b += part)
+    int64_t b = 0;
+    do {   // an empty batch records the hook's events too
         for (size_t ki = 0; ki < p->kernels.size(); ++ki) {
             Kernel& k = p->kernels[ki];
             FftArgs A = k.fft;
@@ -317,11 +310,13 @@ skel_status run_fft(skel_plan p, const skel_buffer* args, hipStream_t s) {
             A.out = res(k.dst);
             A.tw = p->fft_tw;
             A.nfft = (int32_t)std::min(part, B - b);
-            const bool prof = (int)ki == p->prof_kernel;
+            const bool prof = b == 0 && (int)ki == p->prof_kernel;
             if (prof) HIP_TRY(hipEventRecord(p->prof_start, s));
             HIP_TRY(launch_fft_pass(A, k.fft_mode, s));
             if (prof) HIP_TRY(hipEventRecord(p->prof_end, s));
         }
+        b += part;
+    } while (b < B);
     return SKEL_OK;
 }
 
@@ -421,9 +416,9 @@ skel_status ensure_resources(skel_plan p) {
     size_t bytes = 0;
     if (p->lin.dom == DOM_U8) bytes = (size_t)(p->sh.W * p->sh.H * 4);
     if (p->lin.dom == DOM_F32) bytes = (size_t)(p->sh.n * 4);
-    // transposed intermediates take 256 rows of kFftTRow per transform (natural
-    // order between unfused stages takes less)
-    if (p->lin.dom == DOM_C32) bytes = (size_t)p->sh.n * 256 * kFftTRow * 8;
+    // transposed intermediates take 256 rows of kFftTRow per transform of a part
+    // (natural order between unfused stages takes less)
+    if (p->lin.dom == DOM_C32) bytes = (size_t)fft_part(p->sh.n) * 256 * kFftTRow * 8;
     if (p->lin.dom == DOM_GRAY) bytes = (size_t)p->sh.n;
     for (int k = 0; k < nscr; ++k)
         if (!p->scratch[k]) HIP_TRY(hipMalloc(&p->scratch[k], std::max<size_t>(bytes, 16)));

@@ -259,6 +259,17 @@ constexpr int kFftPoints = 65536;
 // passes exchange through plan scratch: 256 + 16 keeps every row on a 128-byte
 // line boundary while breaking the power-of-two stride of the column runs.
 constexpr int kFftTRow = 256 + 16;
+// A batch runs in equal parts of at most kFftRun transforms, each through all
+// passes, so that a part's intermediates (0.54 MB a transform, twice) are still
+// partly in the memory-side cache when the next pass reads them (FFT -> IFFT, us, one
+// part / two: 265 transforms 153 / 163, 285: 175 / 170, 300: 190 / 174, 384: 230 / 216,
+// 512: 318 / 288; parts of 128 lose that again to the launches).
+constexpr int64_t kFftRun = 280;
+// Transforms of a part (the last one may have fewer).
+inline int64_t fft_part(int64_t nfft) {
+    const int64_t parts = (nfft + kFftRun - 1) / kFftRun;
+    return parts > 0 ? (nfft + parts - 1) / parts : 0;
+}
 int fft_cols(int64_t nfft);   // columns (rows) of a transform per work-group
 hipError_t launch_fft_pass(const FftArgs& a, int mode, hipStream_t s);
 const char* fft_pass_name(int mode);

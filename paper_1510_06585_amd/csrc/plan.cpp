@@ -622,8 +622,9 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             Kernel K;
             K.first = first;
             K.last = last;
-            K.wg = 16 * fft_cols(sh.n);
-            K.grid = (int)(sh.n * (256 / fft_cols(sh.n)));
+            const int64_t part = fft_part(sh.n);
+            K.wg = 16 * fft_cols(part);
+            K.grid = (int)(part * (256 / fft_cols(part)));
             K.fft_mode = mode;
             memset(&K.fft, 0, sizeof(K.fft));
             K.fft.dir1 = dir(i);

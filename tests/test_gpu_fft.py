@@ -117,3 +117,40 @@ def test_empty_batch_runs_nothing():
     torch.cuda.synchronize()
     assert y.shape == (0, N, 2)
     p.destroy()
+
+
+@pytest.mark.parametrize("B", [280, 281])
+def test_batches_around_one_and_two_parts(B):
+    """The largest batch that runs in one part, and one in parts of 141 and 140."""
+    _check(synth.complex_batch(synth.SEED_FFT + B, B), ["fft", "ifft"])
+
+
+def test_kernel_events_bracket_the_first_part():
+    """The hook leaves a run of two parts as it is: the same bits with and without it, events around the
+    launch whose grid describe() gives, and none pending for an empty batch."""
+    x = torch.from_numpy(synth.complex_batch(synth.SEED_FFT, 300)).cuda()
+    a, b = [x, torch.empty_like(x)], [x, torch.zeros_like(x)]
+    plan = sk.Plan(sk.image_chain([("fft", {}), ("ifft", {})]), a)
+    assert [k["grid"] for k in plan.describe()["kernels"]] == [150 * 8] * 3
+    plan.run(a)
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for k in range(3):
+        start.record(), end.record()
+        torch.cuda.synchronize()
+        plan.kernel_events(k, start, end)
+        plan.run(b)
+        torch.cuda.synchronize()
+        assert 0 < start.elapsed_time(end) < 50
+        assert torch.equal(a[1], b[1])
+    plan.destroy()
+    empty = [torch.empty(0, 65536, 2, device="cuda") for _ in range(2)]
+    plan = sk.Plan(sk.image_chain([("fft", {})]), empty)
+    before = torch.cuda.Event(enable_timing=True)
+    start.record()
+    before.record()
+    torch.cuda.synchronize()
+    plan.kernel_events(0, start, end)
+    plan.run(empty)
+    torch.cuda.synchronize()
+    assert before.elapsed_time(start) >= 0 and start.elapsed_time(end) >= 0
+    plan.destroy()
