@@ -231,19 +231,20 @@ def _buf_array(bufs):
     return arr, len(bufs)
 
 
-_raw_stream = None   # torch's current-stream handle of a device, without a Stream object
+_raw_stream = None   # torch's getters of a device's current-stream handle and of the current device
 
 
 def _current_stream() -> int:
     """Handle of torch's current stream on the current device.  Building a torch
     Stream object for it takes 2.5 us, 40% of a small run's host time; the raw
-    getter 0.1."""
+    getters 0.1.  They are private to torch: without either, the object is built."""
     global _raw_stream
     import torch
     if _raw_stream is None:
-        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", False)
+        get = [getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice")]
+        _raw_stream = get if all(get) else False
     if _raw_stream and torch.cuda.is_initialized():
-        return _raw_stream(torch._C._cuda_getDevice())
+        return _raw_stream[0](_raw_stream[1]())
     return torch.cuda.current_stream().cuda_stream
 
 

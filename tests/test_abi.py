@@ -380,3 +380,19 @@ def test_default_tile_rows(names, reduce, H, W, wg, rows):
     plan = sk.Plan(sk.image_chain(stages, reduce), args, {"wg": wg})
     assert plan.describe()["kernels"][0]["tile_h"] == rows
     plan.destroy()
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice", None])
+def test_current_stream_without_torchs_private_getters(monkeypatch, missing):
+    """The handle comes from torch's private getters where both are there, else from a Stream object."""
+    import types
+
+    import torch
+    monkeypatch.setattr(sk.skel, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=7))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    if missing:
+        monkeypatch.delattr(torch._C, missing)
+    assert sk.skel._current_stream() == (7 if missing else 103)
