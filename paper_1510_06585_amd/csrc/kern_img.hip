@@ -316,13 +316,15 @@ hipError_t launch_img_batch(const BatchArgs& a, int grid, int wg, hipStream_t s,
 
 int hist_chunk_rows(int bins) { return kSumUnroll * (kFinThreads / bins); }
 
+static bool valid_step(const WhileStep& w) {
+    return w.state && w.cond.channel >= 0 && w.cond.channel <= 3 && w.cond.kind >= 0 && w.cond.kind <= 1 &&
+           !w.merge.acc_hist == !w.merge.it_hist && !w.merge.acc_sum == !w.merge.it_sum;
+}
+
 hipError_t launch_hist_merge(const HistFinArgs& a, hipStream_t s) {
     if (a.bins != 128 && a.bins != 256) return hipErrorInvalidValue;
     if (a.nchunks <= 0) return hipSuccess;
-    const WhileStep& w = a.step;
-    if (w.state && (w.cond.channel < 0 || w.cond.channel > 3 || w.cond.kind < 0 || w.cond.kind > 1 ||
-                    !w.merge.acc_hist != !w.merge.it_hist || !w.merge.acc_sum != !w.merge.it_sum))
-        return hipErrorInvalidValue;
+    if (a.step.state && !valid_step(a.step)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(hist_merge_kernel, dim3(a.nchunks), dim3(kFinThreads), 0, s, a);
     return hipGetLastError();
 }
@@ -348,6 +350,7 @@ hipError_t launch_while_init(uint32_t* state, hipStream_t s) {
 }
 
 hipError_t launch_while_step(const WhileStep& w, hipStream_t s) {
+    if (!valid_step(w)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(while_step_kernel, dim3(1), dim3(kStepThreads), 0, s, w);
     return hipGetLastError();
 }
