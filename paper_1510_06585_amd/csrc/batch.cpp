@@ -182,7 +182,6 @@ extern "C" skel_status skel_batch_run(skel_plan p, const skel_buffer* args, int3
     A.in_flip = K.img.in_flip;
     A.out_flip = K.img.out_flip;
     A.has_hist = red >= 0;
-    A.hist_ks = hist_copies_log2(K.bins, kHistWgWords);
     A.bins = K.bins;
     // streamed loads as well measured slower (1634 against 1515 us on the 256-request batch)
     A.stream = STREAM_OUT;

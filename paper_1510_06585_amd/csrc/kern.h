@@ -66,26 +66,17 @@ struct ImgGroupArgs {
     uint32_t* part;      // histogram epilogue: one row of 4 x bins counts per work-group
     uint32_t* hist;      // reduce outputs cleared by work-group 0 (may be null)
     uint64_t* sum;
-    int32_t bins;        // values emitted are < bins (128 or 256)
+    int32_t bins;        // values emitted are < bins (128 after a last solarise, else 256)
     int32_t W, H;
     int32_t tile_h;      // rows per tile
     int32_t nbands;      // tiles across a row
     int32_t ntiles;      // nbands * ceil(H / tile_h)
     int32_t in_flip, out_flip;
     int32_t write_out;   // 0 for a reduce-only kernel
-    int32_t hist_ks;     // log2 of the histogram copies per bin (see hist_copies_log2)
     int32_t stream;          // STREAM_*
     const uint32_t* guard;   // while Loop: the launch does nothing when *guard == 0 (null: always runs)
     OpList pre, post;
 };
-
-// Output values of a kernel are < bins (128 when the chain's last value stage
-// is a solarise, else 256); the LDS histogram keeps copies = words / bins
-// counters per bin, one per lane class, so equal values in neighbouring lanes
-// hit different words and banks.  Returns log2(copies) for a per-channel
-// region of `words` counters.
-int hist_copies_log2(int bins, int words);
-constexpr int kHistWgWords = 2048;     // per channel, one histogram per work-group
 
 // Compile-time encoding of a value-stage run for specialised kernels:
 // sum of op_k * 4^k; -1 selects the generic stage interpreter.
@@ -191,7 +182,6 @@ struct BatchArgs {
     int32_t has_blur;
     int32_t in_flip, out_flip;
     int32_t has_hist;
-    int32_t hist_ks;     // log2 copies per bin of the work-group histograms
     int32_t bins;        // values emitted are < bins
     int32_t stream;      // STREAM_*
     uint32_t* part;      // histogram rows, one per tile group (ticket)

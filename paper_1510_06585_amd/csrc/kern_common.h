@@ -32,10 +32,6 @@ static __device__ __forceinline__ void st128(u32x4 v, __amdgpu_buffer_rsrc_t r, 
     __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, POLICY);
 }
 template <int POLICY = kTemporal>
-static __device__ __forceinline__ void st64(u32x2 v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, POLICY);
-}
-template <int POLICY = kTemporal>
 static __device__ __forceinline__ void st32(uint32_t v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
     __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, POLICY);
 }

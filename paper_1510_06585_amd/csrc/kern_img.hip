@@ -204,14 +204,6 @@ __global__ void fill_u32_kernel(uint32_t* p, uint64_t n, uint32_t v) {
 }
 
 // ------------------------------------------------------------------ host side
-static_assert(kHistWgChan == kHistWgWords, "histogram layout");
-
-int hist_copies_log2(int bins, int words) {
-    int ks = 0;
-    while ((bins << (ks + 1)) <= words) ++ks;
-    return ks;
-}
-
 int encode_ops(const OpList& l) {
     int e = 0, m = 1;
     for (int k = 0; k < l.n; ++k) {

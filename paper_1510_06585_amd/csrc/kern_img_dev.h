@@ -242,19 +242,22 @@ constexpr int kBlurRing = 6;
 static_assert(kBlurRing == 6, "blur row groups are written out for six slots");
 
 // Histogram modes: none, or one privatised histogram per work-group with
-// kHistWgChan counter words = bins x copies per channel.  HIST_WG: counter
-// (c, v, copy) at word c * kHistWgChan + v * copies + copy.  HIST_WG128
-// (128 bins, 16 copies): at word v * 64 + c * 16 + copy, i.e. byte address
-// v * 256 + c * 64 + 4 * copy, which one byte permute builds from the value
-// byte and the lane's copy offset (c * 64 is the instruction's offset).
+// kHistWgChan counter words = bins x copies per channel, one copy per class of lanes, so
+// that equal values in neighbouring lanes hit different words and banks.  HIST_WG
+// (256 bins, 8 copies): counter (c, v, copy) at word c * kHistWgChan + v * copies +
+// copy.  HIST_WG128 (128 bins, 16 copies; the chain's last value stage is a
+// solarise): at word v * 64 + c * 16 + copy, i.e. byte address v * 256 + c * 64 + 4 *
+// copy, which one byte permute builds from the value byte and the lane's copy offset
+// (c * 64 is the instruction's offset).
 enum { HIST_NONE = 0, HIST_WG = 1, HIST_WG128 = 2 };
+constexpr int kHistWgChan = 2048;
+constexpr int hist_copies(int hm) { return kHistWgChan / (hm == HIST_WG128 ? 128 : 256); }
 // Lanes at either end of a band whose stores are never streamed: 8 x 16 bytes
 // cover the 128-byte line that two bands share (see band_tile).
 constexpr int kEdgeLanes = 8;
 // Kinds of tiles (see band_tile's sweep).
 enum { INTERIOR = 0, EDGE_VEC = 1, EDGE_PX = 2 };
 constexpr int kByArgs = -1;   // a sweep's cache policy as the arguments give it
-constexpr int kHistWgChan = 2048;
 
 // Per-tile geometry and addressing of one image.
 struct ImgView {
@@ -289,7 +292,7 @@ static __device__ __forceinline__ void add_hsum5(const uint32_t (&d)[4], uint32_
 // images of fewer than 4 columns.
 template <int PRE, int POST, bool BLUR, int HM, bool LITE>
 static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList& pre, const OpList& post,
-                                                 int band, int y0, int y1, int lane, uint32_t* lh, int hks) {
+                                                 int band, int y0, int y1, int lane, uint32_t* lh) {
     constexpr bool HIST = HM != HIST_NONE;
     const int W = V.W, H = V.H;
     constexpr int bw = BLUR ? kBandOut : kBandPx;
@@ -302,12 +305,12 @@ static __device__ __forceinline__ void band_tile(const ImgView& V, const OpList&
     const __amdgpu_buffer_rsrc_t rin = mk_rsrc(V.in, nbytes);
     const __amdgpu_buffer_rsrc_t rout = mk_rsrc(V.out, nbytes);
 
-    // Histogram addressing: counter (c, v, copy) lives at word
-    // c * CS + v * 2^hks + copy, copy = lane mod 2^hks; a u16 pair {v0, v1}
-    // shifted left by hks + 2 gives both byte offsets in its halves.
+    // Histogram addressing: a u16 pair {v0, v1} of HIST_WG shifted left by the
+    // counter's size gives both byte offsets in its halves; lane_off is the copy's.
     constexpr int CS = kHistWgChan;
-    const uint32_t hsh = (uint32_t)hks + 2u;
-    const uint32_t lane_off = ((uint32_t)lane & ((1u << hks) - 1u)) * 4u;
+    constexpr uint32_t hsh = HM == HIST_WG128 ? 6 : 5;   // log2 of a counter's bytes over its copies
+    const uint32_t lane_off = ((uint32_t)lane & (uint32_t)(hist_copies(HM) - 1)) * 4u;
+    static_assert(HM == HIST_NONE || 4 * hist_copies(HM) == 1 << hsh, "copies of a counter are adjacent words");
     char* const lhb = reinterpret_cast<char*>(lh);
     auto count = [&](uint32_t e, uint32_t o, uint32_t inc) {
         if constexpr (HM == HIST_WG128) {
@@ -628,6 +631,7 @@ static __device__ __forceinline__ uint32_t quad_add(uint32_t v) {
 // the next tile group.  blockDim.x divides 2048.
 template <int HM, bool CLEAR = false>
 static __device__ __forceinline__ void write_hist_row(uint32_t* lh, uint32_t* row) {
+    static_assert(hist_copies(HIST_WG) == 8 && hist_copies(HIST_WG128) == 16, "2 or 4 lanes to a counter");
     u32x4* const q = reinterpret_cast<u32x4*>(lh);
     for (int t = threadIdx.x; t < kHistWgChan; t += blockDim.x) {
         const u32x4 w = q[t];
@@ -679,11 +683,9 @@ __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_band
         const ImgView V{A.in, A.out, A.W, A.H, FL < 0 ? A.in_flip : (FL & 1), FL < 0 ? A.out_flip : (FL >> 1),
                         A.write_out, A.stream};
         if (HIST && A.bins == 128)
-            band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, LITE>(V, A.pre, A.post, band, y0, y1, lane, lh,
-                                                                       A.hist_ks);
+            band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, LITE>(V, A.pre, A.post, band, y0, y1, lane, lh);
         else
-            band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, LITE>(V, A.pre, A.post, band, y0, y1, lane, lh,
-                                                                    A.hist_ks);
+            band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, LITE>(V, A.pre, A.post, band, y0, y1, lane, lh);
     }
     if constexpr (HIST) {
         __syncthreads();
@@ -746,11 +748,9 @@ __global__ void __launch_bounds__(256, BLUR && PRE != kGeneric ? 4 : 1) img_batc
             const ImgView V{R.in, R.out, R.W, R.H, FL < 0 ? A.in_flip : (FL & 1), FL < 0 ? A.out_flip : (FL >> 1),
                             1, A.stream};
             if (HIST && A.bins == 128)
-                band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, PRE == kGeneric>(V, A.pre, A.post, band, y0, y1, lane, lh,
-                                                                           A.hist_ks);
+                band_tile<PRE, POST, BLUR, HIST ? HIST_WG128 : HIST_NONE, PRE == kGeneric>(V, A.pre, A.post, band, y0, y1, lane, lh);
             else
-                band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, PRE == kGeneric>(V, A.pre, A.post, band, y0, y1, lane, lh,
-                                                                        A.hist_ks);
+                band_tile<PRE, POST, BLUR, HIST ? HIST_WG : HIST_NONE, PRE == kGeneric>(V, A.pre, A.post, band, y0, y1, lane, lh);
         }
         if constexpr (HIST) {
             __syncthreads();

@@ -712,7 +712,6 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             // next iteration: those are kept where that pays.
             const int64_t bytes = sh.W * sh.H * 4;
             A.stream = stream_policy(bytes, K.dst == -2 && !red_sep && !(L.is_while && while_keeps(bytes)));
-            A.hist_ks = hist_copies_log2(bins, kHistWgWords);
             A.bins = bins;
             K.bins = bins;
             K.grid = (A.ntiles + c.wg / 64 - 1) / (c.wg / 64);
@@ -760,7 +759,6 @@ skel_status build_kernels(const Linear& L, const Shape& sh, const Config& c, std
             const int64_t chunks = (sh.H + A.tile_h - 1) / A.tile_h;
             A.ntiles = (sh.W == 0 || sh.H == 0) ? 0 : (int32_t)(A.nbands * chunks);
             A.write_out = 0;
-            A.hist_ks = hist_copies_log2(bins, kHistWgWords);
             A.bins = bins;
             R.bins = bins;
             R.grid = (A.ntiles + c.wg / 64 - 1) / (c.wg / 64);
