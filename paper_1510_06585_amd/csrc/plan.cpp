@@ -501,9 +501,9 @@ int device_cu_count() {
 //    17.2, 9 rows 19.2).
 //  - Where half a round is tiles of at most 3 rows, which load 7, a quarter: one
 //    work-group on every CU (1000 x 1001, us: 5 rows 6.2, 3 rows 6.8; 700^2 3 rows
-//    4.6, 2 rows 5.5); with longer stage lists, which a second wavefront per SIMD
-//    hides less, at most 2 rows (noise, blur, noise, solarise, noise of 1000 x 1001:
-//    5 rows 14.8, 3 rows 13.8).
+//    4.6, 2 rows 5.5); with longer stage lists or noise after the blur, which make
+//    the halo rows a smaller part, at most 2 rows (noise, blur, noise, solarise, noise
+//    of 1000 x 1001: 5 rows 14.8, 3 rows 13.8; blur, noise, noise 7.2 / 6.8).
 //  - Rounds of stencil tiles count kStencilWaves per CU, also where more would fit,
 //    and with a histogram kHistGroups work-groups (64 lanes, 8192^2: 222-row tiles, a
 //    round of 5 groups, 296 us, 273 rows 162).
@@ -534,7 +534,8 @@ static int fitted_tile_h(const ImgGroupArgs& A, bool blur, bool hist, const Conf
         if (x >= 10.0 || waves <= 4) return (int)rows(resident);
         if (waves <= 8) return (int)rows(resident * 0.75);
         const int64_t half = rows(resident / 2);
-        const bool light = A.pre.n <= 2 && A.post.n <= 2;
+        bool light = A.pre.n <= 2 && A.post.n <= 2;
+        for (int k = 0; k < A.post.n; ++k) light &= A.post.op[k] != IOP_NOISE;
         return (int)(half <= (light ? 3 : 2) ? rows(resident / 4) : half);
     }
     int th = std::max(2, (int)std::lround(3.0 * std::sqrt(x)));

@@ -367,6 +367,8 @@ def test_while_loop_option_rejections():
     ("noise,solarise,blur5,mirror", "hist_sum", 1125, 1799, 128, 6),     # three quarters of a round of 8 wavefronts
     ("noise,solarise,blur5,mirror", None, 1000, 1001, 256, 5),           # a quarter: half would be 3 rows
     ("noise,blur5,noise,solarise,noise", None, 1000, 1001, 256, 3),
+    ("blur5,noise,noise", None, 1000, 1001, 256, 3),
+    ("blur5,noise,noise", None, 700, 700, 256, 3),
     ("noise,solarise,mirror", None, 1000, 1001, 256, 2),
     ("noise,solarise,mirror", None, 256, 512, 256, 1),
     ("noise,solarise,mirror", None, 2847, 4289, 256, 3),
