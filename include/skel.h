@@ -447,6 +447,8 @@ skel_status skel_features(skel_node root, const skel_buffer* proto, int32_t narg
  * W3 [1,64], b3 [1].  All pointers are device pointers.
  *  forward   y[i] = MLP(X[i,:]) for X f32 [n,24].
  *  grad      *loss = mean_i (y_i - t_i)^2 and grad f32 [5825] = dloss/dparams.
+ *            The library keeps up to four workspaces of 6 MB per device for
+ *            these calls, taken and given back in stream order.
  *  adam      one Adam step (bias-corrected, step counts from 1) in place on
  *            params, m, v given grad. */
 int32_t skel_mlp_param_count(void);

@@ -19,15 +19,15 @@
 // same way.
 // Twiddles come from the 65536 roots of unity computed in double precision on
 // the host: W_256^(u p) from a 16 x 16 LDS table in the order the threads read
-// it, W_N^(n1 m) as one root per thread times one of a 16 x 32 LDS table.
+// it, W_N^(n1 m) as one root per thread times one of a 16 x COLS LDS table.
 //
 // What bounds it: the three phases of a work-group (load, transform, store) against
 // HBM.  Constant element distances carried in scalar offsets and twiddles read from
 // tables took the VALU instructions of the three modes from 1457 / 2040 / 884 to
 // 1028 / 1709 / 747 with no change in time at 512 transforms.  With streamed results
-// and runs of at most 256 transforms, whose intermediates then partly stay in the
-// memory-side cache, FFT -> IFFT of 512 transforms went from 309 to 299 us, of 256
-// from 160 to 152, of 64 from 47.7 to 41.2; without the runs it is 318 us at 512.
+// and parts of at most kFftRun transforms, whose intermediates then partly stay in the
+// memory-side cache, FFT -> IFFT of 512 transforms went from 306 to 288 us, of 256
+// from 160 to 144, of 64 from 47.7 to 41.2; in one part it is 318 us at 512.
 #include "kern_common.h"
 #include "kern.h"
 
@@ -58,7 +58,7 @@ template <int DIR>
 static __device__ __forceinline__ cpx cmul_i(cpx a) { return DIR < 0 ? cpx{a.y, -a.x} : cpx{-a.y, a.x}; }
 
 // Roots of unity in LDS, W = exp(2 pi i / N): p16[16 p + u] = W_256^(u p), and for
-// the transposed stores row[32 i + j] = W^(16 n1 i) with n1 = 32 g + j.
+// the transposed stores row[COLS i + j] = W^(16 n1 i) with n1 = COLS g + j.
 template <int COLS>
 struct TwLds {
     cpx p16[256], row[16 * COLS];
